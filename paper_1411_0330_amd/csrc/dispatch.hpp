@@ -147,6 +147,15 @@ template <typename T> int launch_xinv(hipStream_t s, const XinvArgs<T>& a, int n
 // the C2R pass of C components (launch_xinv dispatches on the component count)
 template <typename T, int C> int launch_xinv_c(hipStream_t s, const XinvArgs<T>& a, int nload, int variant);
 
+// plane passes (plane.hpp): forward in a mode XF_*, inverse in a mode XI_*
+// (not the fixed-point ones); the ..6 forms are the elastic local term's.  -1 for a plane or mode without an instance.
+template <typename T> struct PlaneFwdArgs;
+template <typename T> struct PlaneInvArgs;
+template <typename T> int launch_pf(hipStream_t s, const PlaneFwdArgs<T>& a, int mode, int nload);
+template <typename T> int launch_pf6(hipStream_t s, const PlaneFwdArgs<T>& a, int nload);
+template <typename T> int launch_pi(hipStream_t s, const PlaneInvArgs<T>& a, int mode, int nload);
+template <typename T> int launch_pi6(hipStream_t s, const PlaneInvArgs<T>& a, int mode, int nload);
+
 // strided-pass shape of a variant: (pencils per workgroup, points per thread)
 template <typename T> constexpr int sv_tx(int n, int p0, int v) {
   const int tx0 = tx_strided<T>(n, p0);

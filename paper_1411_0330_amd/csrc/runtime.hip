@@ -25,6 +25,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "dispatch.hpp"
+#include "plane.hpp"
 #include "solver_kernels.hpp"
 #include "tiny.hpp"
 #include "lsh.h"
@@ -182,6 +183,11 @@ struct lsh_ctx {
   bool gst_dirty = true;
   char* sbuf = nullptr;    // bound solver buffer (MINRES fields)
   size_t sbuf_size = 0;
+  // plane passes (x and y transforms of a plane in one workgroup): geometry
+  // per element type (nvec = 0 where no plane pass applies).  LSH_PLANE=0
+  // keeps the separate x and y passes.
+  bool plane = true;
+  PlaneGeo pgeo[2] = {};   // FP32, FP64
   int tune[2][NPASS] = {{0, 0, 0, 0}, {0, 0, 0, 0}};  // kernel-shape variant per (FP32/FP64, pass)
   // CG breakdown threshold g (|p.Lp| <= g r.r) for FP32 and FP64 fields:
   // eps times a bound of ||L||_2 (max ||(A - A0)^{-1}|| over the phases plus
@@ -457,7 +463,8 @@ void compute_layout(lsh_ctx* ctx) {
   ctx->h_guess.assign(L, 0);
   // partial sums: the largest grid of any reducing kernel, per group
   // (the fused CG step writes the x pass's and the z pass's partials side by side)
-  long long pmax = xinv_blocks(ctx->geo, 2) + zg_blocks_max<float>(ctx->geo);
+  // (the fused CG step's x pass: rows, or one partial per plane and component)
+  long long pmax = std::max(xinv_blocks(ctx->geo, 2), (long long)ctx->geo.nz * c) + zg_blocks_max<float>(ctx->geo);
   pmax = std::max(pmax, (F + 1023) / 1024 + 1);
   ctx->pstride = pmax;
   ctx->off.partials = take(sizeof(double) * L * c * pmax);
@@ -796,6 +803,8 @@ void tune_from_env(lsh_ctx* ctx) {
   if (f && f[0] == '0') ctx->cg_fused = false;
   const char* pe = std::getenv("LSH_PERSISTENT");
   if (pe && pe[0] == '0') ctx->persistent = false;
+  const char* pl = std::getenv("LSH_PLANE");
+  if (pl && pl[0] == '0') ctx->plane = false;
   const char* gs = std::getenv("LSH_GSTORE");
   if (gs && gs[0] == '0') ctx->gstore = false;
   const char* e = std::getenv("LSH_TUNE");
@@ -847,10 +856,80 @@ cpx<T>* paired_spectrum(lsh_ctx* ctx, int l0) {
   return reinterpret_cast<cpx<T>*>(ctx->ptr<char>(ctx->off.s64m)) + (long long)l0 * main_cpx(ctx->geo);
 }
 
+// ------------------------- plane passes ----------------------------------
+// Which planes run as plane passes (the instances of k_plane.hip).  A plane is
+// one workgroup's work, so above 2048 vectors (32 KiB) it also needs at least
+// 48 planes and components per load: fewer leave the chip idle while the
+// separate passes would spread over it (16 x 128 x 128 scalar FP32, 48 of
+// them: 1.03 times as fast; 4 x 192 x 64, 12 of them: 0.8 times).  The number
+// of loads does not count, so that batched and single solves stay bitwise alike.
+template <typename T>
+PlaneGeo plane_geometry(const Geo& g) {
+  PlaneGeo p{};
+  p.nx = g.nx;
+  p.ny = g.ny;
+  p.mx = g.mx;
+  p.pitch = g.mx | 1;
+  p.by_nx = make_fdiv(g.nx);
+  p.by_mx = make_fdiv(g.mx);
+  p.by_ny = make_fdiv(g.ny);
+  p.ax = make_axis(g.mx, sizeof(T) == 4 ? 16 : 8);
+  p.ay = make_axis(g.ny, sizeof(T) == 4 ? 16 : 8);
+  const long long nvec = (long long)g.nx * g.ny * (long long)sizeof(T) / 16;
+  const bool sq = g.nx == g.ny && g.nx >= 16 && g.nx <= (sizeof(T) == 4 ? 160 : 128);
+  const bool fits = sq ? (nvec <= 2048 || (long long)g.nz * g.c >= 48)
+                       : nvec <= 2048 || (sizeof(T) == 4 && nvec <= 3072 && (long long)g.nz * g.c >= 48);
+  if (g.nz > 1 && fits) p.nvec = (int)nvec;
+  return p;
+}
+
+bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+// Whether the x and y passes of this context run as plane passes.
+template <typename T>
+const PlaneGeo* plane_of(lsh_ctx* ctx) {
+  const PlaneGeo& p = ctx->pgeo[sizeof(T) == 8 ? 1 : 0];
+  return (ctx->plane && p.nvec > 0) ? &p : nullptr;
+}
+// Forward in mode xmode: the CG mode needs the local term in its short form.
+template <typename T>
+const PlaneGeo* plane_fwd(lsh_ctx* ctx, int xmode, const void* src) {
+  if (xmode == XF_CG && !ctx->iso) return nullptr;
+  return aligned16(src) ? plane_of<T>(ctx) : nullptr;
+}
+// Inverse in mode `mode` with field tau and output out: the fixed-point modes
+// couple the components of Gamma tau and keep the separate passes, as do
+// phases without the short form (except for the strain, which has no local term).
+template <typename T>
+const PlaneGeo* plane_inv(lsh_ctx* ctx, int mode, const void* tau, const void* out) {
+  if (mode == XI_BASIC || mode == XI_EM) return nullptr;
+  if (mode != XI_STRAIN && !ctx->iso) return nullptr;
+  return (aligned16(tau) && aligned16(out)) ? plane_of<T>(ctx) : nullptr;
+}
+
+template <typename T>
+PlaneFwdArgs<T> plane_fwd_args(lsh_ctx* ctx, const PlaneGeo& p, cpx<T>* sm, cpx<T>* sn, const LoadState* st) {
+  PlaneFwdArgs<T> a{};
+  a.g = ctx->geo;
+  a.p = p;
+  a.smain = sm;
+  a.snyq = sn;
+  a.twx = Sel<T>::tw(ctx, 0);
+  a.twy = Sel<T>::tw(ctx, 1);
+  a.st = st;
+  a.ptab = Sel<T>::ptab(ctx);
+  a.phase = ctx->ptr<uint8_t>(ctx->off.phase);
+  a.vcoef = Sel<T>::vc(ctx);
+  a.nphase = ctx->nphase;
+  a.pstride = (int)ctx->pstride;
+  return a;
+}
+
 // Forward passes on load slots [l0, l0+nload): x (mode), y, z (+Gamma and inverse z), y inverse.
 template <typename T>
 lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src, T* pdir, T* xacc,
-                        const float* dsrc, const LoadState* st, bool gamma, const IrxFold& fold = IrxFold{}) {
+                        const float* dsrc, const LoadState* st, bool gamma, const IrxFold& fold = IrxFold{},
+                        bool skip_yinv = false) {
   const Geo& g = ctx->geo;
   cpx<T>* sm = Sel<T>::sm(ctx) + (long long)l0 * main_cpx(g);
   cpx<T>* sn = Sel<T>::sn(ctx) + (long long)l0 * nyq_cpx(g);
@@ -862,12 +941,21 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
   // CG: read r, p, write p, and (after the first step) read and write x
   const double xin = xmode == XF_CG ? (ctx->xf_first ? 3.0 : 5.0) * cvs
                                     : (xmode == XF_IRX ? 2.0 * cvs + 4.0 * ctx->F : cvs);
-  {
-    Scope sc(ctx, kcls<T>(K_XFWD), nl * (xin + spec));
-    STCHK(check_launch(ctx, launch_xfwd<T>(ctx->stream, xa, nload, tv<T>(ctx, PASS_XFWD)), "x forward"));
-  }
   cpx<T>* sp = gamma ? paired_spectrum<T>(ctx, l0) : nullptr;
-  {
+  const PlaneGeo* pg = (sp || xmode == XF_CG) ? nullptr : plane_fwd<T>(ctx, xmode, src);
+  if (pg) {
+    Scope sc(ctx, kcls<T>(K_XFWD), nl * (xin + spec));
+    PlaneFwdArgs<T> pa = plane_fwd_args<T>(ctx, *pg, sm, sn, st);
+    pa.src = src;
+    pa.pout = pdir;
+    pa.dsrc = dsrc;
+    pa.fold = fold;
+    STCHK(check_launch(ctx, launch_pf<T>(ctx->stream, pa, xmode, nload), "x and y forward"));
+  } else {
+    {
+      Scope sc(ctx, kcls<T>(K_XFWD), nl * (xin + spec));
+      STCHK(check_launch(ctx, launch_xfwd<T>(ctx->stream, xa, nload, tv<T>(ctx, PASS_XFWD)), "x forward"));
+    }
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = sp ? launch_y_paired<T>(ctx->stream, g, -1, sm, sp, sn, Sel<T>::tw(ctx, 1), st, nload,
                                            tv<T>(ctx, PASS_Y))
@@ -884,7 +972,7 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
                                      st, nload, tv<T>(ctx, PASS_ZG));
     STCHK(check_launch(ctx, nb, "z/Green"));
   }
-  if (gamma) {
+  if (gamma && !skip_yinv) {
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = sp ? launch_y_paired<T>(ctx->stream, g, 1, sm, sp, sn, Sel<T>::tw(ctx, 1), st, nload,
                                            tv<T>(ctx, PASS_Y))
@@ -897,7 +985,7 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
 template <typename T>
 lsh_status inverse_x(lsh_ctx* ctx, int l0, int nload, int mode, const T* tau, T* out, float* rout,
                      const LoadState* st, double* partials, int* nparts, const T* rin = nullptr,
-                     bool paired = false) {
+                     bool paired = false, const PlaneGeo* pg = nullptr) {
   const Geo& g = ctx->geo;
   XinvArgs<T> a{};
   a.g = g;
@@ -936,10 +1024,29 @@ lsh_status inverse_x(lsh_ctx* ctx, int l0, int nload, int mode, const T* tau, T*
   if (mode == XI_IRRES) bytes += 4.0 * ctx->F;                                  // FP32 residual out
   else if (mode != XI_RESNORM) bytes += cvs;                                    // real output
   Scope sc(ctx, kcls<T>(K_XINV), nl * bytes);
-  const int nb = launch_xinv<T>(ctx->stream, a, nload, tv<T>(ctx, PASS_XINV));
+  int nb;
+  if (pg) {
+    PlaneInvArgs<T> pa{g, *pg, a.smain, a.snyq, a.twx, Sel<T>::tw(ctx, 1), tau, out, rin, rout, a.ptab, a.phase,
+                       a.vcoef, a.loads, st, partials, a.pstride, ctx->nphase, a.scale};
+    nb = launch_pi<T>(ctx->stream, pa, mode, nload);
+  } else {
+    nb = launch_xinv<T>(ctx->stream, a, nload, tv<T>(ctx, PASS_XINV));
+  }
   STCHK(check_launch(ctx, nb, "x inverse"));
   if (nparts) *nparts = nb;
   return LSH_OK;
+}
+
+// One whole application on load slots [l0, l0+nload): the forward passes of
+// src (x mode `xmode`), Gamma, and the inverse passes with the epilogue `mode`
+// on the field tau (the field transformed).
+template <typename T>
+lsh_status operator_pass(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src, T* pdir, const float* dsrc,
+                         const LoadState* st, int mode, const T* tau, T* out, float* rout, double* partials,
+                         int* nparts, const IrxFold& fold = IrxFold{}) {
+  const PlaneGeo* pg = paired_shape<T>(ctx) ? nullptr : plane_inv<T>(ctx, mode, tau, out);
+  STCHK(forward_part<T>(ctx, l0, nload, xmode, src, pdir, nullptr, dsrc, st, true, fold, pg != nullptr));
+  return inverse_x<T>(ctx, l0, nload, mode, tau, out, rout, st, partials, nparts, nullptr, false, pg);
 }
 
 lsh_status scal(lsh_ctx* ctx, int mode, int ngroups, int nparts, LoadState* st, double tol, int l0 = 0,
@@ -973,15 +1080,26 @@ lsh_status cg_fused_step(lsh_ctx* ctx, int l0, int nload, T* x, T* r, const T* p
   XfwdcArgs<T> xa{g, r, pin, pout, x, sm, sn, Sel<T>::tw(ctx, 0), st, ctx->nphase, ctx->iso, Sel<T>::ptab(ctx),
                   ctx->ptr<uint8_t>(ctx->off.phase), Sel<T>::vc(ctx), parts, (int)ctx->pstride, pr ? 1 : 0};
   int nbx = 0, nbz = 0, nbi = 0;
-  {
-    // fields: first step r in, p out; then r and p_{k-1} in, p_k out, and every
-    // second step (two pending updates) p_{k-2} and x in, x out as well
-    const double fields = ctx->xf_first ? 2.0 : (par == 0 ? 6.0 : 3.0);
+  const PlaneGeo* pg = pr ? nullptr : plane_inv<T>(ctx, XI_CGR, pout, r);
+  // fields: first step r in, p out; then r and p_{k-1} in, p_k out, and every
+  // second step (two pending updates) p_{k-2} and x in, x out as well
+  const double fields = ctx->xf_first ? 2.0 : (par == 0 ? 6.0 : 3.0);
+  if (pg) {
     Scope sc(ctx, kcls<T>(K_XFWD), nl * (fields * cvs + spec + mat));
-    nbx = launch_xfwdc<T>(ctx->stream, xa, nload);
-    STCHK(check_launch(ctx, nbx, "x forward (CG)"));
-  }
-  {
+    PlaneFwdArgs<T> pa = plane_fwd_args<T>(ctx, *pg, sm, sn, st);
+    pa.src = r;
+    pa.pin = pin;
+    pa.pout = pout;
+    pa.x = x;
+    pa.partials = parts;
+    nbx = launch_pf<T>(ctx->stream, pa, XF_CG, nload);
+    STCHK(check_launch(ctx, nbx, "x and y forward (CG)"));
+  } else {
+    {
+      Scope sc(ctx, kcls<T>(K_XFWD), nl * (fields * cvs + spec + mat));
+      nbx = launch_xfwdc<T>(ctx->stream, xa, nload);
+      STCHK(check_launch(ctx, nbx, "x forward (CG)"));
+    }
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = pr ? launch_y_paired_inplace<T>(ctx->stream, g, -1, sm, sn, Sel<T>::tw(ctx, 1), st, nload,
                                                    tv<T>(ctx, PASS_Y))
@@ -999,14 +1117,14 @@ lsh_status cg_fused_step(lsh_ctx* ctx, int l0, int nload, T* x, T* r, const T* p
     STCHK(check_launch(ctx, nbz, "z/Green"));
   }
   if (scalars) STCHK(scal(ctx, SC_ALPHA, nload, nbx + nbz, st, ctx->bd_guard[sizeof(T) == 8 ? 1 : 0], l0, par));
-  {
+  if (!pg) {
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = pr ? launch_y_paired_inplace<T>(ctx->stream, g, 1, sm, sn, Sel<T>::tw(ctx, 1), st, nload,
                                                    tv<T>(ctx, PASS_Y))
                       : launch_y<T>(ctx->stream, g, 1, sm, sn, Sel<T>::tw(ctx, 1), st, nload, tv<T>(ctx, PASS_Y));
     STCHK(check_launch(ctx, nb, "y inverse"));
   }
-  STCHK(inverse_x<T>(ctx, l0, nload, XI_CGR, pout, r, nullptr, st, parts, &nbi, r, pr));
+  STCHK(inverse_x<T>(ctx, l0, nload, XI_CGR, pout, r, nullptr, st, parts, &nbi, r, pr, pg));
   return scalars ? scal(ctx, SC_BETA, nload, nbi, st, 0.0, l0) : LSH_OK;
 }
 
@@ -1069,9 +1187,9 @@ lsh_status guess_init(lsh_ctx* ctx, int nload, double* x, double* r, LoadState* 
     STCHK(check_launch(ctx, 0, "guess mask"));
   }
   if (r == nullptr) return cg_init<double>(ctx, nload, nullptr, nullptr, st, tol);
-  STCHK(forward_part<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, nullptr, nullptr, true));
   double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
-  STCHK(inverse_x<double>(ctx, 0, nload, XI_APPLY, x, q, nullptr, nullptr, nullptr, nullptr));
+  STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, nullptr, XI_APPLY, x, q, nullptr, nullptr,
+                              nullptr));
   {
     Scope sc(ctx, K_INIT);
     hipLaunchKernelGGL((k_guessinit<double>), dim3(nb, nload), dim3(256), 0, ctx->stream, g, q, r,
@@ -1237,9 +1355,9 @@ lsh_status basic_loop(lsh_ctx* ctx, int nload, double* x, LoadState* st, size_t 
   for (auto& s : hst) any |= s.active != 0, ctx->nact += s.active != 0;
   if (!any) return LSH_OK;
   auto iteration = [&]() -> lsh_status {
-    STCHK(forward_part<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, nullptr, st, true));
     int np = 0;
-    STCHK(inverse_x<double>(ctx, 0, nload, ximode, x, x, nullptr, st, ctx->ptr<double>(ctx->off.partials), &np));
+    STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, st, ximode, x, x, nullptr,
+                                ctx->ptr<double>(ctx->off.partials), &np));
     return scal(ctx, SC_BASIC, nload, np, st, 0.0);
   };
   for (int it = 0; it < maxit; ++it) {
@@ -1295,9 +1413,8 @@ lsh_status mr_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
   double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
   const int nbe = (int)((F + 256 * kEwUnroll - 1) / (256 * kEwUnroll));
   for (int it = 0; it < maxit; ++it) {
-    STCHK(forward_part<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, nullptr, st, true));
     int np = 0;
-    STCHK(inverse_x<double>(ctx, 0, nload, XI_CG, v, q, nullptr, st, parts, &np));
+    STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, st, XI_CG, v, q, nullptr, parts, &np));
     {
       Scope sc(ctx, K_SCAL);
       hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(256), 0, ctx->stream, (int)MR_ALPHA, parts, (int)ctx->pstride,
@@ -1369,9 +1486,8 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
   double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
   const int nbe = (int)((F + 256 * kEwUnroll - 1) / (256 * kEwUnroll));
   for (int it = 0; it < maxit; ++it) {
-    STCHK(forward_part<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, nullptr, st, true));
     int np = 0;
-    STCHK(inverse_x<double>(ctx, 0, nload, XI_CG, v, q, nullptr, st, parts, &np));
+    STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, st, XI_CG, v, q, nullptr, parts, &np));
     {
       Scope sc(ctx, K_SCAL);
       hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(256), 0, ctx->stream, (int)MR_ALPHA, parts, (int)ctx->pstride,
@@ -1410,10 +1526,9 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
 // ||b - L x||^2 per load into sums[0..nload) (FP64 application on x64)
 lsh_status true_residual(lsh_ctx* ctx, int nload) {
   double* x = ctx->ptr<double>(ctx->off.x64);
-  STCHK(forward_part<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, nullptr, nullptr, true));
   int np = 0;
-  STCHK(inverse_x<double>(ctx, 0, nload, XI_RESNORM, x, nullptr, nullptr, nullptr,
-                          ctx->ptr<double>(ctx->off.partials), &np));
+  STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, nullptr, XI_RESNORM, x, nullptr, nullptr,
+                              ctx->ptr<double>(ctx->off.partials), &np));
   return scal(ctx, SC_SUM, nload, np, nullptr, 0.0);
 }
 
@@ -1483,8 +1598,8 @@ lsh_status timing_iteration(lsh_ctx* ctx, int nload, bool fp64) {
   LoadState* st = ctx->ptr<LoadState>(ctx->off.st_out);
   double* x = ctx->ptr<double>(ctx->off.x64);
   if (ctx->precision == LSH_MIXED) {
-    STCHK(forward_part<double>(ctx, 0, nload, XF_IRX, nullptr, x, nullptr, ctx->ptr<float>(ctx->off.d32), st, true));
-    return inverse_x<double>(ctx, 0, nload, XI_IRRES, x, nullptr, ctx->ptr<float>(ctx->off.r32), st, parts, nullptr);
+    return operator_pass<double>(ctx, 0, nload, XF_IRX, nullptr, x, ctx->ptr<float>(ctx->off.d32), st, XI_IRRES, x,
+                                 nullptr, ctx->ptr<float>(ctx->off.r32), parts, nullptr);
   }
   double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
   STCHK(forward_part<double>(ctx, 0, nload, XF_CG, ctx->ptr<double>(ctx->off.r64), ctx->ptr<double>(ctx->off.p64), x,
@@ -1684,6 +1799,8 @@ lsh_status lsh_create(lsh_ctx** out, int dim, const int64_t* n, int physics, int
   ctx->A0.assign((size_t)ctx->c * ctx->c, 0.0);
   compute_layout(ctx);
   tune_from_env(ctx);
+  ctx->pgeo[0] = plane_geometry<float>(ctx->geo);
+  ctx->pgeo[1] = plane_geometry<double>(ctx->geo);
   *out = ctx;
   return LSH_OK;
 }
@@ -1883,8 +2000,8 @@ lsh_status lsh_gradient(lsh_ctx* ctx, const double* W, void* grad, int dtype) {
   // strain estimates p_l - Gamma tau_l of every solved load, in the FP64 spectrum buffer
   double* x = ctx->ptr<double>(ctx->off.x64);
   double* eps = reinterpret_cast<double*>(Sel<double>::sm(ctx));
-  STCHK(forward_part<double>(ctx, 0, L, XF_PLAIN, x, nullptr, nullptr, nullptr, nullptr, true));
-  STCHK(inverse_x<double>(ctx, 0, L, XI_STRAIN, x, eps, nullptr, nullptr, nullptr, nullptr));
+  STCHK(operator_pass<double>(ctx, 0, L, XF_PLAIN, x, nullptr, nullptr, nullptr, XI_STRAIN, x, eps, nullptr, nullptr,
+                              nullptr));
   HIPCHK(hipMemcpyAsync(ctx->ws + ctx->off.wgrad, w.data(), sizeof(double) * w.size(), hipMemcpyHostToDevice,
                         ctx->stream));
   const Geo& g = ctx->geo;
@@ -2093,11 +2210,10 @@ lsh_status lsh_solve(lsh_ctx* ctx, int solver, int nload, const double* loads, d
         TraceRange tr_ref("lsh_solve: FP64 refinement residual");
         // x64 += d plus the inner solve's pending steps (x64 = that, on the first pass from zero)
         const IrxFold fold{p, ctx->cg_fused ? ctx->ptr<float>(ctx->off.p32b) : nullptr, sti, xzero ? 1 : 0};
-        STCHK(forward_part<double>(ctx, 0, nload, XF_IRX, nullptr, x64, nullptr, d, sto, true, fold));
-        xzero = false;
         int np = 0;
-        STCHK(inverse_x<double>(ctx, 0, nload, XI_IRRES, x64, nullptr, r, sto, ctx->ptr<double>(ctx->off.partials),
-                                &np));
+        STCHK(operator_pass<double>(ctx, 0, nload, XF_IRX, nullptr, x64, d, sto, XI_IRRES, x64, nullptr, r,
+                                    ctx->ptr<double>(ctx->off.partials), &np, fold));
+        xzero = false;
         STCHK(scal(ctx, SC_OUTER, nload, np, sto, 0.0));
       }
       ++outer;
@@ -2281,9 +2397,9 @@ lsh_status lsh_get_field(lsh_ctx* ctx, int load, int which, void* dst, int dtype
   double* x = ctx->ptr<double>(ctx->off.x64) + (long long)load * F;
   if (which == LSH_FIELD_TAU) return copy_field_out(ctx, x, F, dst, dtype, mem);
   // strain p - Gamma tau, computed into the FP64 spectrum slot of this load
-  STCHK(forward_part<double>(ctx, load, 1, XF_PLAIN, x, nullptr, nullptr, nullptr, nullptr, true));
   double* out = reinterpret_cast<double*>(Sel<double>::sm(ctx) + (long long)load * main_cpx(ctx->geo));
-  STCHK(inverse_x<double>(ctx, load, 1, XI_STRAIN, x, out, nullptr, nullptr, nullptr, nullptr));
+  STCHK(operator_pass<double>(ctx, load, 1, XF_PLAIN, x, nullptr, nullptr, nullptr, XI_STRAIN, x, out, nullptr, nullptr,
+                              nullptr));
   return copy_field_out(ctx, out, F, dst, dtype, mem);
 }
 
@@ -2297,15 +2413,13 @@ lsh_status lsh_apply(lsh_ctx* ctx, int nload, const void* tau, void* out, int dt
     return fail(ctx, LSH_EINVAL, "FP32 application needs a mixed-precision context");
   STCHK(prepare(ctx));
   if (dtype == LSH_F64) {
-    STCHK(forward_part<double>(ctx, 0, nload, XF_PLAIN, static_cast<const double*>(tau), nullptr, nullptr, nullptr,
-                               nullptr, true));
-    STCHK(inverse_x<double>(ctx, 0, nload, XI_APPLY, static_cast<const double*>(tau), static_cast<double*>(out),
-                            nullptr, nullptr, nullptr, nullptr));
+    STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, static_cast<const double*>(tau), nullptr, nullptr, nullptr,
+                            XI_APPLY, static_cast<const double*>(tau), static_cast<double*>(out), nullptr, nullptr,
+                            nullptr));
   } else {
-    STCHK(forward_part<float>(ctx, 0, nload, XF_PLAIN, static_cast<const float*>(tau), nullptr, nullptr, nullptr,
-                              nullptr, true));
-    STCHK(inverse_x<float>(ctx, 0, nload, XI_APPLY, static_cast<const float*>(tau), static_cast<float*>(out), nullptr,
-                           nullptr, nullptr, nullptr));
+    STCHK(operator_pass<float>(ctx, 0, nload, XF_PLAIN, static_cast<const float*>(tau), nullptr, nullptr, nullptr,
+                            XI_APPLY, static_cast<const float*>(tau), static_cast<float*>(out), nullptr, nullptr,
+                            nullptr));
   }
   ctx->have_solution = false;
   HIPCHK(hipStreamSynchronize(ctx->stream));
@@ -2332,17 +2446,13 @@ lsh_status lsh_apply_noalloc(lsh_ctx* ctx, int nload, const void* tau, void* out
   ctx->ovr_sn = sp;
   lsh_status s;
   if (dtype == LSH_F64) {
-    s = forward_part<double>(ctx, 0, nload, XF_PLAIN, static_cast<const double*>(tau), nullptr, nullptr, nullptr,
-                             nullptr, true);
-    if (s == LSH_OK)
-      s = inverse_x<double>(ctx, 0, nload, XI_APPLY, static_cast<const double*>(tau), static_cast<double*>(out),
-                            nullptr, nullptr, nullptr, nullptr);
+    s = operator_pass<double>(ctx, 0, nload, XF_PLAIN, static_cast<const double*>(tau), nullptr, nullptr, nullptr,
+                              XI_APPLY, static_cast<const double*>(tau), static_cast<double*>(out), nullptr, nullptr,
+                              nullptr);
   } else {
-    s = forward_part<float>(ctx, 0, nload, XF_PLAIN, static_cast<const float*>(tau), nullptr, nullptr, nullptr,
-                            nullptr, true);
-    if (s == LSH_OK)
-      s = inverse_x<float>(ctx, 0, nload, XI_APPLY, static_cast<const float*>(tau), static_cast<float*>(out), nullptr,
-                           nullptr, nullptr, nullptr);
+    s = operator_pass<float>(ctx, 0, nload, XF_PLAIN, static_cast<const float*>(tau), nullptr, nullptr, nullptr,
+                             XI_APPLY, static_cast<const float*>(tau), static_cast<float*>(out), nullptr, nullptr,
+                             nullptr);
   }
   ctx->ovr_sm = nullptr;
   ctx->ovr_sn = nullptr;
@@ -2488,6 +2598,11 @@ lsh_status lsh_autotune(lsh_ctx* ctx, int nload, const char* cache_path, int32_t
     for (int pi = 0; pi < NPASS; ++pi) {
       const int pass = order[pi];
       if (!pass_has_variants(ctx, pass)) continue;
+      // x and y run as plane passes, which have one shape
+      const bool paired = !fp64 && paired_shape<float>(ctx);
+      const bool planes = fp64 ? plane_inv<double>(ctx, XI_APPLY, nullptr, nullptr) != nullptr
+                               : plane_inv<float>(ctx, XI_APPLY, nullptr, nullptr) != nullptr;
+      if (planes && !paired && pass != PASS_ZG) continue;
       // the fused CG x pass has one shape (CG fields: FP32 of a mixed context, FP64 of an FP64 one)
       if (pass == PASS_XFWD && ctx->cg_fused && (!fp64 || ctx->precision != LSH_MIXED)) continue;
       const int cls = pass_class(pass, fp64);
