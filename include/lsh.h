@@ -353,7 +353,12 @@ lsh_status lsh_spectrum_bytes(const lsh_ctx* ctx, int dtype, size_t* bytes);
  * filtered operator, 128- or 256-point y and z axes; otherwise shape 0 runs;
  * the copy lives in the FP64 spectrum buffer of the workspace, so the
  * workspace size does not change).  Every shape computes the
- * same result up to rounding; only speed differs.  lsh_get_variants writes the 8 current
+ * same result up to rounding; only speed differs.  Grids whose x-y planes fit
+ * one workgroup (squares up to 160 x 160 in FP32 and 128 x 128 in FP64, and
+ * other small planes; three dimensions, isotropic phases or per-voxel moduli)
+ * run x and y as one pass of one shape whatever these choices say (z shape 5
+ * excepted); LSH_PLANE=0 in the environment keeps the separate passes.
+ * lsh_get_variants writes the 8 current
  * choices (FP32 passes, then FP64).  The environment variable LSH_TUNE (for
  * example "zg32=1,xinv64=2") sets them when the context is created.
  */

@@ -71,6 +71,7 @@ struct XfwdArgs {
   const cpx<T>* twx;
   const LoadState* st;
   IrxFold fold;   // XF_IRX: the inner solve's pending steps, x starting at zero
+  unsigned long long* prog;   // see progress_push
 };
 
 // Kernel-shape variants of each pass (0 = the default shape).  For the axis

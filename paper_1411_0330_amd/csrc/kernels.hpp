@@ -63,6 +63,20 @@ __device__ __forceinline__ void hist_push(const HistRef& h, const int load, cons
   e[1] = (double)h.level;
 }
 
+// Progress of a load as the host sees it: iterations done and whether the load
+// still iterates, in a word of pinned host memory per load (null: none), which
+// the first kernel of every iteration publishes as it starts, so that the write
+// to the host passes while that kernel runs (at the end of the scalar kernel it
+// held up the next one by about 2 us).  The host reads the word without queueing
+// a copy or waiting for the stream.  Bit 0: written, bit 1: still iterating, then
+// the iterations; relaxed, since the host reads nothing else before it has
+// waited for the stream, and a release would write the whole L2 back.
+__device__ __forceinline__ void progress_push(unsigned long long* prog, const int load, const LoadState& L) {
+  if (prog != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(prog + load, ((unsigned long long)(unsigned)L.iters << 2) | (L.active ? 3ull : 1ull),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The FP64 refinement x pass of a mixed solve (XF_IRX, x += d) also applies
 // the x updates that the FP32 inner CG left pending (one or two steps, from
 // the direction buffers its load states name: pa, or pa and pb for the fused
@@ -163,7 +177,8 @@ __global__ __launch_bounds__(256) void k_xfwd(const Geo g, const int mode, const
                                               T* __restrict__ pdir, T* __restrict__ xacc,
                                               const float* __restrict__ dsrc, cpx<T>* __restrict__ smain,
                                               cpx<T>* __restrict__ snyq, const cpx<T>* __restrict__ twx,
-                                              const LoadState* __restrict__ st, const IrxFold fold) {
+                                              const LoadState* __restrict__ st, const IrxFold fold,
+                                              unsigned long long* prog) {
   constexpr int TR = MX / P;
   constexpr int RPW = 256 / TR;
   constexpr int SEG = TR * (int)sizeof(cpx<T>);   // contiguous bytes per access instruction
@@ -176,6 +191,7 @@ __global__ __launch_bounds__(256) void k_xfwd(const Geo g, const int mode, const
   const long long row = (long long)blockIdx.x * RPW + slot;
   const bool valid = row < rows;
   const long long roff = (long long)l * field_elems(g) + row * (2 * MX);
+  if (st != nullptr) progress_push(prog, l, st[l]);
   if (st != nullptr && !st[l].active) {
     // a load that is not refined still gets its zero start written (x was not zeroed)
     if (mode == XF_IRX && fold.xzero && valid) {
@@ -405,6 +421,7 @@ struct XfwdcArgs {
   double* partials;
   int pstride;
   int paired;     // write the main spectrum in the component-paired layout (FP32, even c)
+  unsigned long long* prog;
 };
 
 template <typename T, int MX, int P, int C>
@@ -422,6 +439,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(xfwdc_waves
   __shared__ double red[4];
   const Geo& g = a.g;
   const int l = blockIdx.y;
+  progress_push(a.prog, l, a.st[l]);
   if (!a.st[l].active) return;
   const int tid = threadIdx.x;
   const int slot = tid / TR, t = tid % TR;

@@ -320,6 +320,7 @@ struct PlaneFwdArgs {
   double* partials;
   int pstride, nphase;
   IrxFold fold;
+  unsigned long long* prog;
 };
 
 template <int NT>
@@ -400,6 +401,7 @@ __global__ __launch_bounds__(NT) void k_pf(const PlaneFwdArgs<T> a) {
   const long long plane = (long long)p.nx * p.ny;
   const long long fo = (long long)l * field_elems(g) + (long long)z * plane;   // component 0 of this plane
   const long long co = fo + (long long)j * g.nvox;
+  if (a.st != nullptr) progress_push(a.prog, l, a.st[l]);
   if (a.st != nullptr && !a.st[l].active) {
     // a load that is not refined still gets its zero start written (x was not zeroed)
     if (XF == XF_IRX && a.fold.xzero) {

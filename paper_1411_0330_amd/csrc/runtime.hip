@@ -21,6 +21,7 @@
 
 #include <sys/mman.h>
 #include <ucontext.h>
+#include <x86intrin.h>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
 
@@ -241,6 +242,8 @@ struct lsh_ctx {
     long long key = -1;
   } graphs[5];   // CG FP64, CG FP32, fixed point; CG FP64 and FP32 of odd iterations (fused step)
   long long graph_epoch = 0;  // bumped whenever captured kernel arguments may change
+  unsigned long long* prog = nullptr;   // progress words of the running iteration loop (see progress_push)
+  std::string graph_args;     // the material's kernel arguments at the last bump (values, see build_tables)
 
   // timing
   bool timing = false;
@@ -389,14 +392,21 @@ lsh_status wait_stream(lsh_ctx* ctx) {
   return LSH_OK;
 }
 
-// Pinned staging: the LoadState records of max_loads loads, then max_loads c doubles.
+// Pinned staging: the LoadState records of max_loads loads, then max_loads c
+// doubles, then a progress word per load (progress_push).
+size_t progress_offset(const lsh_ctx* ctx) {
+  return align_up(sizeof(LoadState) * ctx->max_loads + sizeof(double) * ctx->max_loads * ctx->c);
+}
 lsh_status pinned(lsh_ctx* ctx, void** out) {
   if (!ctx->hpin) {
-    const size_t bytes = sizeof(LoadState) * ctx->max_loads + sizeof(double) * ctx->max_loads * ctx->c;
-    HIPCHK(hipHostMalloc(&ctx->hpin, bytes, hipHostMallocDefault));
+    HIPCHK(hipHostMalloc(&ctx->hpin, progress_offset(ctx) + sizeof(unsigned long long) * ctx->max_loads,
+                         hipHostMallocDefault));
   }
   *out = ctx->hpin;
   return LSH_OK;
+}
+unsigned long long* progress_words(lsh_ctx* ctx) {
+  return reinterpret_cast<unsigned long long*>(static_cast<char*>(ctx->hpin) + progress_offset(ctx));
 }
 
 // Copy n bytes from the device into host memory h through the pinned staging
@@ -688,7 +698,22 @@ lsh_status build_tables(lsh_ctx* ctx) {
   }
   STCHK(wait_stream(ctx));
   ctx->tables_dirty = false;
-  ctx->graph_epoch++;
+  // Captured iterations hold the material's scalars as kernel arguments; its
+  // tables, phase ids and coefficients are read from the workspace.  A new
+  // microstructure with the same scalars keeps the graphs (capturing and
+  // instantiating them again cost 0.3 to 0.5 ms a solve).
+  std::string args(reinterpret_cast<const char*>(&gp), sizeof(gp));
+  auto add = [&](const void* v, size_t n) { args.append(static_cast<const char*>(v), n); };
+  add(&ctx->nphase, sizeof(ctx->nphase));
+  add(&ctx->iso, sizeof(ctx->iso));
+  add(&ctx->mat_voxel, sizeof(ctx->mat_voxel));
+  add(ctx->bd_guard, sizeof(ctx->bd_guard));
+  add(ctx->A0.data(), sizeof(double) * ctx->A0.size());
+  add(&ctx->gtab, sizeof(ctx->gtab));
+  if (args != ctx->graph_args) {
+    ctx->graph_args = args;
+    ctx->graph_epoch++;
+  }
   return LSH_OK;
 }
 
@@ -922,6 +947,7 @@ PlaneFwdArgs<T> plane_fwd_args(lsh_ctx* ctx, const PlaneGeo& p, cpx<T>* sm, cpx<
   a.vcoef = Sel<T>::vc(ctx);
   a.nphase = ctx->nphase;
   a.pstride = (int)ctx->pstride;
+  a.prog = ctx->prog;
   return a;
 }
 
@@ -933,7 +959,7 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
   const Geo& g = ctx->geo;
   cpx<T>* sm = Sel<T>::sm(ctx) + (long long)l0 * main_cpx(g);
   cpx<T>* sn = Sel<T>::sn(ctx) + (long long)l0 * nyq_cpx(g);
-  XfwdArgs<T> xa{g, xmode, src, pdir, xacc, dsrc, sm, sn, Sel<T>::tw(ctx, 0), st, fold};
+  XfwdArgs<T> xa{g, xmode, src, pdir, xacc, dsrc, sm, sn, Sel<T>::tw(ctx, 0), st, fold, ctx->prog};
   // algorithmic bytes per launch (loads still iterating x per-load traffic)
   const double nl = std::min(ctx->nact, nload);
   const double cvs = (double)ctx->F * sizeof(T);
@@ -1078,7 +1104,7 @@ lsh_status cg_fused_step(lsh_ctx* ctx, int l0, int nload, T* x, T* r, const T* p
   // the paired z shape: every pass of the step in place on the paired layout
   const bool pr = paired_shape<T>(ctx);
   XfwdcArgs<T> xa{g, r, pin, pout, x, sm, sn, Sel<T>::tw(ctx, 0), st, ctx->nphase, ctx->iso, Sel<T>::ptab(ctx),
-                  ctx->ptr<uint8_t>(ctx->off.phase), Sel<T>::vc(ctx), parts, (int)ctx->pstride, pr ? 1 : 0};
+                  ctx->ptr<uint8_t>(ctx->off.phase), Sel<T>::vc(ctx), parts, (int)ctx->pstride, pr ? 1 : 0, ctx->prog};
   int nbx = 0, nbz = 0, nbi = 0;
   const PlaneGeo* pg = pr ? nullptr : plane_inv<T>(ctx, XI_CGR, pout, r);
   // fields: first step r in, p out; then r and p_{k-1} in, p_k out, and every
@@ -1232,9 +1258,74 @@ lsh_status read_states(lsh_ctx* ctx, size_t off, int nload, std::vector<LoadStat
   return read_back(ctx, h.data(), ctx->ws + off, sizeof(LoadState) * nload, 0);
 }
 
-int check_period(lsh_ctx* ctx, int nload) {
-  const long long work = ctx->geo.nvox * (long long)nload * ctx->c;
-  return work >= (1LL << 22) ? 1 : 8;
+// The iteration loops queue iteration k + 1 when the GPU has begun iteration k,
+// which tells the host the outcome of iteration k - 1: the GPU does not wait for
+// the host, and one iteration whose kernels all return at once follows
+// convergence.  (Reading the states back after every iteration left the GPU idle
+// for about 20 us each time; every eighth iteration on small grids queued up to
+// seven empty ones.)  A Progress spans a loop; h are the states just read, so
+// nothing queued writes the words.
+struct Progress {
+  lsh_ctx* ctx;
+  explicit Progress(lsh_ctx* c, const std::vector<LoadState>& h) : ctx(c) {
+    unsigned long long* w = progress_words(ctx);
+    ctx->nact = 0;
+    for (size_t l = 0; l < h.size(); ++l) {
+      __atomic_store_n(w + l, 0ull, __ATOMIC_RELEASE);
+      ctx->nact += h[l].active != 0;
+    }
+    ctx->prog = w;
+  }
+  ~Progress() { ctx->prog = nullptr; }
+  Progress(const Progress&) = delete;
+  Progress& operator=(const Progress&) = delete;
+};
+
+// Waits until every load of h that was active has done `done` iterations of the
+// running loop or has stopped; *any tells whether one still iterates.  The
+// stream bounds the wait: after 50 ms without an answer it is asked for errors
+// and completion (not sooner: a query can queue a marker behind the iteration).
+lsh_status progress_wait(lsh_ctx* ctx, const std::vector<LoadState>& h, int done, bool* any) {
+  const unsigned long long* w = progress_words(ctx);
+  auto asked = std::chrono::steady_clock::now();
+  for (unsigned spin = 1;; ++spin) {
+    bool ready = true;
+    int act = 0;
+    for (size_t l = 0; l < h.size(); ++l) {
+      if (!h[l].active) continue;
+      const unsigned long long v = __atomic_load_n(w + l, __ATOMIC_ACQUIRE);
+      const bool stopped = (v & 3) == 1;
+      act += stopped ? 0 : 1;
+      if (!stopped && (v == 0 || (long long)(v >> 2) < done)) ready = false;
+    }
+    *any = act > 0;
+    ctx->nact = act;
+    if (ready) return LSH_OK;
+    if (spin % 1024 == 0 && std::chrono::steady_clock::now() - asked > std::chrono::milliseconds(50)) {
+      asked = std::chrono::steady_clock::now();
+      const hipError_t q = hipStreamQuery(ctx->stream);
+      if (q == hipSuccess) {
+        // everything queued has finished: the words are final
+        bool late = true;
+        for (size_t l = 0; l < h.size(); ++l) {
+          const unsigned long long v = __atomic_load_n(w + l, __ATOMIC_ACQUIRE);
+          if (h[l].active && (v & 3) != 1 && (v == 0 || (long long)(v >> 2) < done)) late = false;
+        }
+        if (!late) return fail(ctx, LSH_EHIP, "an iteration ended without reporting its state");
+        continue;
+      }
+      if (q != hipErrorNotReady) return fail(ctx, LSH_EHIP, std::string("stream query: ") + hipGetErrorString(q));
+    }
+    if (t_fibers.cur != nullptr) {
+      fiber_yield();
+      if (ctx->ws_device >= 0) {
+        int cur = -1;
+        if (hipGetDevice(&cur) == hipSuccess && cur != ctx->ws_device) HIPCHK(hipSetDevice(ctx->ws_device));
+      }
+    } else {
+      _mm_pause();
+    }
+  }
 }
 
 // Queue one solver iteration.  With graphs enabled (and kernel timing off)
@@ -1283,13 +1374,11 @@ lsh_status run_iteration(lsh_ctx* ctx, int slot, long long key, F&& enqueue) {
 template <typename T>
 lsh_status cg_loop(lsh_ctx* ctx, int nload, T* x, T* r, T* p, T* pb, LoadState* st, size_t st_off, int maxit,
                    std::vector<LoadState>& hst, bool flush = true) {
-  const int period = check_period(ctx, nload);
   T* q = reinterpret_cast<T*>(Sel<T>::sm(ctx));
   STCHK(read_states(ctx, st_off, nload, hst));
-  bool any = false;
-  ctx->nact = 0;
-  for (auto& s : hst) any |= s.active != 0, ctx->nact += s.active != 0;
-  if (!any) return LSH_OK;
+  const Progress progress(ctx, hst);
+  if (ctx->nact == 0) return LSH_OK;
+  bool any = true;
   if (ctx->persistent && ctx->cg_fused && tiny_grid(ctx->geo)) {
     // the whole loop in one launch: one workgroup per load
     TinyArgs<T> ta{};
@@ -1332,13 +1421,8 @@ lsh_status cg_loop(lsh_ctx* ctx, int nload, T* x, T* r, T* p, T* pb, LoadState* 
     ctx->xf_first = it == 0;
     par = ctx->cg_fused ? (it & 1) : 0;
     STCHK(run_iteration(ctx, (sizeof(T) == 8 ? 0 : 1) + 3 * par, key, iteration));
-    if ((it + 1) % period == 0 || it + 1 == maxit) {
-      STCHK(read_states(ctx, st_off, nload, hst));
-      any = false;
-      ctx->nact = 0;
-      for (auto& s : hst) any |= s.active != 0, ctx->nact += s.active != 0;
-      if (!any) break;
-    }
+    STCHK(progress_wait(ctx, hst, it, &any));
+    if (!any) break;
   }
   ctx->xf_first = false;
   // without flush the caller applies the pending steps (the mixed path's refinement pass)
@@ -1348,12 +1432,10 @@ lsh_status cg_loop(lsh_ctx* ctx, int nload, T* x, T* r, T* p, T* pb, LoadState* 
 // Fixed-point schemes on tau in place: basic (XI_BASIC) or Eyre--Milton (XI_EM).
 lsh_status basic_loop(lsh_ctx* ctx, int nload, double* x, LoadState* st, size_t st_off, int maxit,
                       std::vector<LoadState>& hst, int ximode = XI_BASIC) {
-  const int period = check_period(ctx, nload);
   STCHK(read_states(ctx, st_off, nload, hst));
-  bool any = false;
-  ctx->nact = 0;
-  for (auto& s : hst) any |= s.active != 0, ctx->nact += s.active != 0;
-  if (!any) return LSH_OK;
+  const Progress progress(ctx, hst);
+  if (ctx->nact == 0) return LSH_OK;
+  bool any = true;
   auto iteration = [&]() -> lsh_status {
     int np = 0;
     STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, x, nullptr, nullptr, st, ximode, x, x, nullptr,
@@ -1362,13 +1444,8 @@ lsh_status basic_loop(lsh_ctx* ctx, int nload, double* x, LoadState* st, size_t 
   };
   for (int it = 0; it < maxit; ++it) {
     STCHK(run_iteration(ctx, 2, (long long)nload * 8 + ximode, iteration));
-    if ((it + 1) % period == 0 || it + 1 == maxit) {
-      STCHK(read_states(ctx, st_off, nload, hst));
-      any = false;
-      ctx->nact = 0;
-      for (auto& s : hst) any |= s.active != 0, ctx->nact += s.active != 0;
-      if (!any) break;
-    }
+    STCHK(progress_wait(ctx, hst, it, &any));
+    if (!any) break;
   }
   return LSH_OK;
 }
@@ -1404,12 +1481,10 @@ lsh_status mr_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
                        st, ms, hist_ref(ctx, 0, 0));
     STCHK(check_launch(ctx, 0, "minres init"));
   }
-  const int period = check_period(ctx, nload);
   STCHK(read_states(ctx, ctx->off.st_out, nload, hst));
-  ctx->nact = 0;
-  bool any = false;
-  for (auto& sv : hst) any |= sv.active != 0, ctx->nact += sv.active != 0;
-  if (!any) return LSH_OK;
+  const Progress progress(ctx, hst);
+  if (ctx->nact == 0) return LSH_OK;
+  bool any = true;
   double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
   const int nbe = (int)((F + 256 * kEwUnroll - 1) / (256 * kEwUnroll));
   for (int it = 0; it < maxit; ++it) {
@@ -1440,13 +1515,8 @@ lsh_status mr_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
     }
     std::swap(v, vp);    // v_{k+1} now in the old v_{k-1} slot
     std::swap(w1, w2);   // w_k now in the old w_{k-2} slot
-    if ((it + 1) % period == 0 || it + 1 == maxit) {
-      STCHK(read_states(ctx, ctx->off.st_out, nload, hst));
-      any = false;
-      ctx->nact = 0;
-      for (auto& sv : hst) any |= sv.active != 0, ctx->nact += sv.active != 0;
-      if (!any) break;
-    }
+    STCHK(progress_wait(ctx, hst, it, &any));
+    if (!any) break;
   }
   return LSH_OK;
 }
@@ -1477,12 +1547,10 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
                        0, st, ms, hist_ref(ctx, 0, 0));
     STCHK(check_launch(ctx, 0, "symmlq init"));
   }
-  const int period = check_period(ctx, nload);
   STCHK(read_states(ctx, ctx->off.st_out, nload, hst));
-  ctx->nact = 0;
-  bool any = false;
-  for (auto& sv : hst) any |= sv.active != 0, ctx->nact += sv.active != 0;
-  if (!any) return LSH_OK;
+  const Progress progress(ctx, hst);
+  if (ctx->nact == 0) return LSH_OK;
+  bool any = true;
   double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
   const int nbe = (int)((F + 256 * kEwUnroll - 1) / (256 * kEwUnroll));
   for (int it = 0; it < maxit; ++it) {
@@ -1512,13 +1580,8 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
       STCHK(check_launch(ctx, 0, "symmlq update"));
     }
     std::swap(v, vp);    // v_{k+1} now in the old v_{k-1} slot
-    if ((it + 1) % period == 0 || it + 1 == maxit) {
-      STCHK(read_states(ctx, ctx->off.st_out, nload, hst));
-      any = false;
-      ctx->nact = 0;
-      for (auto& sv : hst) any |= sv.active != 0, ctx->nact += sv.active != 0;
-      if (!any) break;
-    }
+    STCHK(progress_wait(ctx, hst, it, &any));
+    if (!any) break;
   }
   return LSH_OK;
 }
