@@ -43,9 +43,13 @@ UNITS = [
     ("k_y.hip", "k_y_f64.o", ["-DLSH_Y_TYPE=double"]),
     ("k_z.hip", "k_z_f32.o", ["-DLSH_Z_TYPE=float"]),
     ("k_z.hip", "k_z_f64.o", ["-DLSH_Z_TYPE=double"]),
+    ("k_z.hip", "k_zf_f32.o", ["-DLSH_Z_TYPE=float", "-DLSH_Z_FLAT"]),
+    ("k_z.hip", "k_zf_f64.o", ["-DLSH_Z_TYPE=double", "-DLSH_Z_FLAT"]),
     ("k_z.hip", "k_zs_f32.o", ["-DLSH_Z_TYPE=float", "-DLSH_Z_STORED"]),
     ("k_z.hip", "k_zs_f64.o", ["-DLSH_Z_TYPE=double", "-DLSH_Z_STORED"]),
     *[("k_plane.hip", f"k_p{part}_{n}.o", [f"-DLSH_P_TYPE={t}", f"-DLSH_P_PART={part}"])
+      for part in range(4) for n, t in (("f32", "float"), ("f64", "double"))],
+    *[("k_plane.hip", f"k_r{part}_{n}.o", [f"-DLSH_P_TYPE={t}", f"-DLSH_P_PART={part}", "-DLSH_P_ROWS"])
       for part in range(4) for n, t in (("f32", "float"), ("f64", "double"))],
     ("k_tiny.hip", "k_tiny_f32.o", ["-DLSH_TINY_TYPE=float"]),
     ("k_tiny.hip", "k_tiny_f64.o", ["-DLSH_TINY_TYPE=double"]),

@@ -124,6 +124,10 @@ template <typename T> int launch_zg_paired(hipStream_t s, const Geo& g, const Gr
 template <typename T> int launch_zg(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb,
                                     int zmode, cpx<T>* sm, cpx<T>* sn, const cpx<T>* tw, const LoadState* st,
                                     int nload, int variant = 0, double* qpart = nullptr, int pstride = 0);
+// the Green pass of 2D grids, with both y transforms; g is the grid as nx x 1 x ny
+template <typename T> int launch_zg_flat(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb,
+                                         int zmode, cpx<T>* sm, cpx<T>* sn, const cpx<T>* tw, const LoadState* st,
+                                         int nload, double* qpart, int pstride);
 // the Green pass with the stored operator tb.st (3D, three or six components;
 // -1 elsewhere); launch_zg forwards to it when tb.st is bound
 template <typename T> int launch_zg_stored(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb,
@@ -156,6 +160,12 @@ template <typename T> int launch_pf(hipStream_t s, const PlaneFwdArgs<T>& a, int
 template <typename T> int launch_pf6(hipStream_t s, const PlaneFwdArgs<T>& a, int nload);
 template <typename T> int launch_pi(hipStream_t s, const PlaneInvArgs<T>& a, int mode, int nload);
 template <typename T> int launch_pi6(hipStream_t s, const PlaneInvArgs<T>& a, int mode, int nload);
+// the same kernels as x passes over blocks of rows (the y pass follows or
+// precedes); -1 for a row length or row count without an instance
+template <typename T> int launch_rf(hipStream_t s, const PlaneFwdArgs<T>& a, int mode, int nload);
+template <typename T> int launch_rf6(hipStream_t s, const PlaneFwdArgs<T>& a, int nload);
+template <typename T> int launch_ri(hipStream_t s, const PlaneInvArgs<T>& a, int mode, int nload);
+template <typename T> int launch_ri6(hipStream_t s, const PlaneInvArgs<T>& a, int mode, int nload);
 
 // strided-pass shape of a variant: (pencils per workgroup, points per thread)
 template <typename T> constexpr int sv_tx(int n, int p0, int v) {

@@ -1,6 +1,7 @@
-// Plane passes (x and y transforms of a plane in one workgroup): instances of
-// one element type (LSH_P_TYPE) and part (LSH_P_PART: 0 and 1 forward, 2 and 3
-// inverse, for scalar and elastic fields).
+// Plane passes (x and y transforms of a plane in one workgroup) and, with
+// LSH_P_ROWS, the x passes over blocks of rows: instances of one element type
+// (LSH_P_TYPE) and part (LSH_P_PART: 0 and 1 forward, 2 and 3 inverse, for
+// scalar and elastic fields).
 #include "plane.hpp"
 
 #include "dispatch.hpp"
@@ -11,6 +12,7 @@
 
 namespace lsh {
 
+#ifndef LSH_P_ROWS
 // Threads and vectors per thread of a square plane of nvec 16-byte vectors:
 // about four a thread, and above LIM vectors 1024 threads.  The forward pass
 // of conjugate gradients and the plain one take LIM = 4608 (FP32 up to 128 x
@@ -58,14 +60,63 @@ static int plane_config(const PlaneGeo& p, F&& f) {
   }
   return -1;
 }
+#else
+
+template <typename T, int LIM, typename F>
+static int plane_config(const PlaneGeo& p, F&& f) {
+  using std::integral_constant;
+  auto rb = [&](auto n_) {
+    constexpr int N = decltype(n_)::value;
+    auto go = [&](auto small_) {
+      constexpr int RB = rows_per_block<T>(N, decltype(small_)::value);
+      using G = PlaneFix<T, N, RB, false>;
+      constexpr int NT = (G::nvec / 4 + 63) / 64 * 64, K = (G::nvec + NT - 1) / NT;
+      if (p.ny % RB != 0) return -1;   // p.ny: all rows of a component
+      return f(integral_constant<int, NT>{}, integral_constant<int, K>{}, G{});
+    };
+    return p.nvec == 2 ? go(std::true_type{}) : go(std::false_type{});
+  };
+  switch (p.nx) {
+    case 48: return rb(integral_constant<int, 48>{});
+    case 64: return rb(integral_constant<int, 64>{});
+    case 80: return rb(integral_constant<int, 80>{});
+    case 96: return rb(integral_constant<int, 96>{});
+    case 128: return rb(integral_constant<int, 128>{});
+    case 160: return rb(integral_constant<int, 160>{});
+    case 192: return rb(integral_constant<int, 192>{});
+    case 256: return rb(integral_constant<int, 256>{});
+    case 512: return rb(integral_constant<int, 512>{});
+    case 1024: return rb(integral_constant<int, 1024>{});
+    default: return -1;
+  }
+}
+
+#define launch_pf launch_rf
+#define launch_pf6 launch_rf6
+#define launch_pi launch_ri
+#define launch_pi6 launch_ri6
+#endif
+
+// grid and dynamic LDS of an instance: planes or row blocks, times components
+template <typename T, typename P>
+static int plane_blocks(const Geo& g) {
+  if constexpr (P::kY) return g.nz * g.c;
+  else return (int)((long long)g.nz * g.ny / P::ny) * g.c;
+}
+template <typename T, typename P>
+static size_t plane_lds_of(const PlaneGeo& p) {
+  if constexpr (P::kStatic) return plane_lds_bytes<T>(P::nx, P::ny, P::pitch);
+  else return plane_lds_bytes<T>(p.nx, p.ny, p.pitch);
+}
 
 template <typename T, bool EL, int XF>
 static int pf_inst(hipStream_t s, const PlaneFwdArgs<T>& a, int nload) {
   return plane_config<T, (XF == XF_IRX ? 2560 : 4608)>(a.p, [&](auto nt_, auto k_, auto geo_) {
     constexpr int NT = decltype(nt_)::value, K = decltype(k_)::value;
-    const int nb = a.g.nz * a.g.c;
-    hipLaunchKernelGGL((k_pf<T, NT, K, EL, XF, decltype(geo_)>), dim3(nb, nload), dim3(NT),
-                       plane_lds_bytes<T>(a.p.nx, a.p.ny, a.p.pitch), s, a);
+    using P = decltype(geo_);
+    const int nb = plane_blocks<T, P>(a.g);
+    const size_t lds = plane_lds_of<T, P>(a.p);
+    hipLaunchKernelGGL((k_pf<T, NT, K, EL, XF, P>), dim3(nb, nload), dim3(NT), lds, s, a);
     return nb;
   });
 }
@@ -74,9 +125,10 @@ template <typename T, bool EL, int MODE>
 static int pi_inst(hipStream_t s, const PlaneInvArgs<T>& a, int nload) {
   return plane_config<T, 2560>(a.p, [&](auto nt_, auto k_, auto geo_) {
     constexpr int NT = decltype(nt_)::value, K = decltype(k_)::value;
-    const int nb = a.g.nz * a.g.c;
-    hipLaunchKernelGGL((k_pi<T, NT, K, EL, MODE, decltype(geo_)>), dim3(nb, nload), dim3(NT),
-                       plane_lds_bytes<T>(a.p.nx, a.p.ny, a.p.pitch), s, a);
+    using P = decltype(geo_);
+    const int nb = plane_blocks<T, P>(a.g);
+    const size_t lds = plane_lds_of<T, P>(a.p);
+    hipLaunchKernelGGL((k_pi<T, NT, K, EL, MODE, P>), dim3(nb, nload), dim3(NT), lds, s, a);
     return nb;
   });
 }

@@ -2,7 +2,8 @@
 // (LSH_Z_TYPE) so that FP32 and FP64 compile in parallel.  Built twice per
 // type: without LSH_Z_STORED the operator is formed on the fly (launch_zg);
 // with it, from the stored table (launch_zg_stored, three- and
-// six-component 3D fields), in a unit of its own so both compile in parallel.
+// six-component 3D fields), in a unit of its own so both compile in parallel;
+// and with LSH_Z_FLAT the pass of 2D grids (launch_zg_flat).
 #include "dispatch.hpp"
 
 namespace lsh {
@@ -27,6 +28,53 @@ static int z_inst(hipStream_t s, const Geo& g, const GreenParams& gp, const Gree
   return main_tiles + nyq_tiles;
 }
 
+#ifdef LSH_Z_FLAT
+// 2D: the y transforms, Gamma and the inverse y transforms in one pass, as the
+// last axis of an nx x 1 x ny grid.  Two components a thread; 64-byte row
+// segments (two tiles of a line on one XCD) rather than whole lines, since a 2D
+// grid has few pencils (512 x 512 FP64 x 2 loads: the three passes took 10.2 +
+// 9.6 + 10.2 us).
+template <typename T, int NL>
+static int z2(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb, int zmode, cpx<T>* sm,
+              cpx<T>* sn, const cpx<T>* tw, const LoadState* st, int nload, double* qp, int ps) {
+  constexpr int P = odd_part(NL) > 1 ? p_odd<T>(NL, 4) : cmin(8, NL);
+  constexpr int TX = cmax((int)(64 / sizeof(cpx<T>)), cmin(64, 64 * P / NL));
+  // a quarter of the pencils (16-byte segments) where that leaves few workgroups
+  constexpr int TXS = cmin(TX, cmax(TX / 4, cmax(1, 64 * P / NL)));
+  if constexpr (TXS < TX) {
+    if (g.mx / TX < 32) return z_inst<T, NL, 2, TXS, P>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
+  }
+  return z_inst<T, NL, 2, TX, P>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
+}
+
+template <typename T>
+int launch_zg_flat(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb, int zmode, cpx<T>* sm,
+                   cpx<T>* sn, const cpx<T>* tw, const LoadState* st, int nload, double* qp, int ps) {
+  if (g.ny != 1) return -1;
+  switch (g.nz) {
+#define LSH_Z2(N) \
+  case N: return z2<T, N>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps)
+    LSH_Z2(2);
+    LSH_Z2(4);
+    LSH_Z2(8);
+    LSH_Z2(16);
+    LSH_Z2(32);
+    LSH_Z2(64);
+    LSH_Z2(128);
+    LSH_Z2(256);
+    LSH_Z2(512);
+    LSH_Z2(1024);
+    LSH_Z2(48);
+    LSH_Z2(96);
+    LSH_Z2(192);
+    LSH_Z2(80);
+    LSH_Z2(160);
+#undef LSH_Z2
+    default: return -1;
+  }
+}
+#else
+
 template <typename T, int NZ, int C>
 static int zm_inst(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb, cpx<T>* sm,
                    cpx<T>* sn, const cpx<T>* tw, const LoadState* st, int nload, double* qp, int ps) {
@@ -44,10 +92,10 @@ static int zm_inst(hipStream_t s, const Geo& g, const GreenParams& gp, const Gre
 template <typename T, int NZ, int C, int V>
 static int z_var(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb, int zmode, cpx<T>* sm,
                  cpx<T>* sn, const cpx<T>* tw, const LoadState* st, int nload, double* qp, int ps) {
-  constexpr int P0 = (NZ == 1) ? 1 : p_z<T, C>(NZ);
-  constexpr int TX0 = (NZ == 1) ? 64 : tx_strided<T>(NZ, P0);
+  constexpr int P0 = p_z<T, C>(NZ);
+  constexpr int TX0 = tx_strided<T>(NZ, P0);
   constexpr int TXV = sv_tx<T>(NZ, P0, V), PV = sv_p(P0, V);
-  if constexpr (V != 0 && NZ > 1 && sv_ok<T>(NZ, TXV, PV))
+  if constexpr (V != 0 && sv_ok<T>(NZ, TXV, PV))
     return z_inst<T, NZ, C, TXV, PV>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
   else
     return z_inst<T, NZ, C, TX0, P0>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
@@ -122,10 +170,7 @@ int launch_zg_paired(hipStream_t s, const Geo& g, const GreenParams& gp, const G
 template <typename T>
 int launch_zg(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb, int zmode, cpx<T>* sm,
               cpx<T>* sn, const cpx<T>* tw, const LoadState* st, int nload, int v, double* qp, int ps) {
-  if (g.c == 2) {
-    if (g.nz != 1) return -1;
-    return z_one<T, 1, 2>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
-  }
+  if (g.c == 2) return launch_zg_flat<T>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
   // the stored operator (where bound) serves the Green pass of every shape
   // except the multi-load one (4), which forms its matrices itself
   if (zmode == Z_GAMMA && tb.st != nullptr && g.nz > 1 && v != 4)
@@ -135,11 +180,16 @@ int launch_zg(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTab
   return -1;
 }
 #endif
+#endif  // LSH_Z_FLAT
 
 #ifndef LSH_Z_TYPE
 #error "define LSH_Z_TYPE"
 #endif
-#ifdef LSH_Z_STORED
+#ifdef LSH_Z_FLAT
+template int launch_zg_flat<LSH_Z_TYPE>(hipStream_t, const Geo&, const GreenParams&, const GreenTabs<LSH_Z_TYPE>&, int,
+                                        cpx<LSH_Z_TYPE>*, cpx<LSH_Z_TYPE>*, const cpx<LSH_Z_TYPE>*, const LoadState*,
+                                        int, double*, int);
+#elif defined(LSH_Z_STORED)
 template int launch_zg_stored<LSH_Z_TYPE>(hipStream_t, const Geo&, const GreenParams&, const GreenTabs<LSH_Z_TYPE>&,
                                           cpx<LSH_Z_TYPE>*, cpx<LSH_Z_TYPE>*, const cpx<LSH_Z_TYPE>*,
                                           const LoadState*, int, int, double*, int);

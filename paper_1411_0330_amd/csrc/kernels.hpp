@@ -866,7 +866,8 @@ __global__ __launch_bounds__(TX*(NZ / P)) __attribute__((amdgpu_waves_per_eu(PR 
           stored_matrix<T, C>(sq + i * skz, sgs, Gm);
           sym_apply<T, C>(Gm, w);
         } else {
-          const int k[3] = {kx, ky, kz};
+          // 2D: the pencil runs along y (ny = 1 here)
+          const int k[3] = {kx, C == 2 ? kz : ky, C == 2 ? 0 : kz};
           const long long tidx = (kx < g.mx) ? ((long long)kz * g.ny + ky) * g.mx + kx
                                              : (long long)g.nz * g.ny * g.mx + (long long)kz * g.ny + ky;
           green_apply<T, C>(gp, tb, k, tidx, w);

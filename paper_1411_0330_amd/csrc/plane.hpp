@@ -17,6 +17,11 @@
 // is bounded by LDS alone.  Axis lengths are run-time values: radices 3 or 5
 // first, then powers of two, so every later span is a power of two.
 //
+// Without the y transform (blocks of rows instead of planes) the same kernels
+// are the x passes of larger grids: 192^3 elastic FP64 x 2 loads 824 and 592 us
+// a pass in registers (280 and 356 of them, one wave per SIMD), 716 and 542
+// here; 160^3 scalar FP64 353 and 317 -> 277 and 219 us.
+//
 // Measured against the separate passes, x + y forward and y + x inverse in CG:
 // 64^3 elastic FP32 x 6 loads 41.5 + 21.3 and 21.3 + 36.0 us -> 40.3 and 39.7;
 // 128^3 scalar FP32 x 3 82 + 31 and 31 + 65 -> 88 and 68; 96^3 elastic FP32 x 6
@@ -55,7 +60,7 @@ struct PlaneAxis {
 };
 
 struct PlaneGeo {
-  static constexpr bool kStatic = false;
+  static constexpr bool kStatic = false, kY = true;
   int nx, ny, mx, pitch, nvec, pad;   // nvec: 16-byte vectors of one real plane (= of its half spectrum)
   FDiv by_nx, by_mx, by_ny;
   PlaneAxis ax, ay;                   // ax: the mx-point transform of the packed rows
@@ -94,16 +99,32 @@ constexpr PlaneAxis make_axis(int n, int rmax) {
 }
 
 // The same with the axis lengths at compile time (every index and span a
-// constant): square planes of the lengths that cubic grids have.
-template <typename T, int N>
-struct PlaneSq {
-  static constexpr bool kStatic = true;
-  static constexpr int nx = N, ny = N, mx = N / 2, pitch = mx | 1, nvec = N * N * (int)sizeof(T) / 16;
+// constant): square planes of the lengths that cubic grids have
+// (Y), or blocks of NY whole rows whose y transform is left to the y pass.
+template <typename T, int NX, int NY, bool Y>
+struct PlaneFix {
+  static constexpr bool kStatic = true, kY = Y;
+  static constexpr int nx = NX, ny = NY, mx = NX / 2, pitch = mx | 1, nvec = NX * NY * (int)sizeof(T) / 16;
   static constexpr PlaneAxis ax = make_axis(mx, sizeof(T) == 4 ? 16 : 8), ay = make_axis(ny, sizeof(T) == 4 ? 16 : 8);
   __device__ __forceinline__ int div_nx(int n) const { return n / nx; }
   __device__ __forceinline__ int div_mx(int n) const { return n / mx; }
   __device__ __forceinline__ int div_ny(int n) const { return n / ny; }
 };
+
+// Row blocks: lengths with an instance, and rows per workgroup: 1024 16-byte
+// vectors (768 or 1280 of lengths 3 and 5 times a power of two), or a quarter of
+// them where that leaves fewer than 256 workgroups per load.
+constexpr bool row_length(int n) {
+  return n == 48 || n == 64 || n == 80 || n == 96 || n == 128 || n == 160 || n == 192 || n == 256 || n == 512 || n == 1024;
+}
+template <typename T> constexpr int rows_per_block(int n, bool small) {
+  int r = 1;
+  while (r * 2 * n * (int)sizeof(T) / 16 <= 1280 || (r * n * (int)sizeof(T) / 16) % 256 != 0) r *= 2;
+  return small ? (r >= 4 ? r / 4 : 1) : r;
+}
+inline bool rows_small(const Geo& g, int rb) { return (long long)g.nz * g.ny / rb * g.c < 256; }
+
+template <typename T, int N> using PlaneSq = PlaneFix<T, N, N, true>;
 
 template <typename P>
 __device__ __forceinline__ decltype(auto) plane_geo(const PlaneGeo& p) {
@@ -226,9 +247,13 @@ template <typename T, int NT, typename P>
 __device__ __forceinline__ void plane_tables(const PlaneLds<T>& s, const P& p, const cpx<T>* twx,
                                              const cpx<T>* twy) {
   for (int i = threadIdx.x; i < p.nx; i += NT) s.twx[i] = twx[i];
-  for (int i = threadIdx.x; i < p.ny; i += NT) s.twy[i] = twy[i];
+  if constexpr (P::kY) {
+    for (int i = threadIdx.x; i < p.ny; i += NT) s.twy[i] = twy[i];
+  }
   for (int i = threadIdx.x; i < p.mx; i += NT) s.px[i] = (uint16_t)plane_pos(p.ax, i);
-  for (int i = threadIdx.x; i < p.ny; i += NT) s.py[i] = (uint16_t)plane_pos(p.ay, i);
+  if constexpr (P::kY) {
+    for (int i = threadIdx.x; i < p.ny; i += NT) s.py[i] = (uint16_t)plane_pos(p.ay, i);
+  }
 }
 
 // (in-I0 flag, a, b) of each phase's short form a Id + b m m^T
@@ -323,6 +348,21 @@ struct PlaneFwdArgs {
   unsigned long long* prog;
 };
 
+// Workgroup id -> (plane or row block, component): the components of a plane go
+// to one XCD (ids are dealt round-robin to the 8 XCDs), one after another, so
+// that the trace's second reads come from its L2.
+__device__ __forceinline__ void plane_block(const int id, const int nblk, const int c, int& z, int& j) {
+  const int full = nblk / 8 * 8 * c;
+  if (id < full) {
+    const int r = id % (8 * c);
+    z = id / (8 * c) * 8 + r % 8;
+    j = r / 8;
+  } else {
+    z = id / c;
+    j = id % c;
+  }
+}
+
 template <int NT>
 __device__ __forceinline__ double plane_sum(double v, double* red) {
 #pragma unroll
@@ -362,7 +402,7 @@ __device__ __forceinline__ void plane_forward(const PlaneLds<T>& s, const P& p, 
     }
   }
   __syncthreads();
-  plane_fft<-1, false, T, NT>(s.buf, p, s.twy);
+  if constexpr (P::kY) plane_fft<-1, false, T, NT>(s.buf, p, s.twy);
   constexpr int CV = 16 / sizeof(cpx<T>);   // complex values per 16 bytes
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -371,11 +411,15 @@ __device__ __forceinline__ void plane_forward(const PlaneLds<T>& s, const P& p, 
       const int e = q * CV;
       const int ky = p.div_mx(e);
       const int kx = e - ky * p.mx;
-      const cpx<T>* row = s.buf + s.py[ky] * p.pitch;
+      const cpx<T>* row = s.buf + (P::kY ? s.py[ky] : ky) * p.pitch;
       cpx<T> o[CV];
 #pragma unroll
       for (int i = 0; i < CV; ++i) o[i] = row[s.px[kx + i]];
-      if (kx == 0) {
+      if (!P::kY && kx == 0) {
+        no[ky] = cpx<T>{o[0].y, T(0)};
+        o[0].y = T(0);
+      }
+      if (P::kY && kx == 0) {
         const cpx<T> c = o[0], m = s.buf[s.py[ky == 0 ? 0 : p.ny - ky] * p.pitch];
         o[0] = cpx<T>{T(0.5) * (c.x + m.x), T(0.5) * (c.y - m.y)};
         no[ky] = cpx<T>{T(0.5) * (c.y + m.y), T(0.5) * (m.x - c.x)};
@@ -397,7 +441,9 @@ __global__ __launch_bounds__(NT) void k_pf(const PlaneFwdArgs<T> a) {
   decltype(auto) p = plane_geo<P>(a.p);
   const Geo& g = a.g;
   const int l = blockIdx.y, tid = threadIdx.x;
-  const int z = (int)blockIdx.x / g.c, j = (int)blockIdx.x % g.c;
+  const int nblk = (int)gridDim.x / g.c;
+  int z, j;
+  plane_block((int)blockIdx.x, nblk, g.c, z, j);
   const long long plane = (long long)p.nx * p.ny;
   const long long fo = (long long)l * field_elems(g) + (long long)z * plane;   // component 0 of this plane
   const long long co = fo + (long long)j * g.nvox;
@@ -533,8 +579,8 @@ __global__ __launch_bounds__(NT) void k_pf(const PlaneFwdArgs<T> a) {
   }
   __syncthreads();
   plane_forward<T, NT, K>(s, p,
-                          a.smain + (long long)l * main_cpx(g) + ((long long)j * g.nz + z) * p.ny * p.mx,
-                          a.snyq + (long long)l * nyq_cpx(g) + ((long long)j * g.nz + z) * p.ny);
+                          a.smain + (long long)l * main_cpx(g) + ((long long)j * nblk + z) * p.ny * p.mx,
+                          a.snyq + (long long)l * nyq_cpx(g) + ((long long)j * nblk + z) * p.ny);
   if constexpr (XF == XF_CG) {
     const double sum = plane_sum<NT>(part, s.red);
     if (tid == 0) a.partials[(long long)l * a.pstride + blockIdx.x] = sum;
@@ -588,13 +634,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves<
   const Geo& g = a.g;
   const int l = blockIdx.y, tid = threadIdx.x;
   if (a.st != nullptr && !a.st[l].active) return;
-  const int z = (int)blockIdx.x / g.c, j = (int)blockIdx.x % g.c;
+  const int nblk = (int)gridDim.x / g.c;
+  int z, j;
+  plane_block((int)blockIdx.x, nblk, g.c, z, j);
   const long long plane = (long long)p.nx * p.ny;
   const long long fo = (long long)l * field_elems(g) + (long long)z * plane;
   const long long co = fo + (long long)j * g.nvox;
   const PlaneLds<T> s = plane_lds<T>(plane_mem, p);
-  const cpx<T>* so = a.smain + (long long)l * main_cpx(g) + ((long long)j * g.nz + z) * p.ny * p.mx;
-  const cpx<T>* no = a.snyq + (long long)l * nyq_cpx(g) + ((long long)j * g.nz + z) * p.ny;
+  const cpx<T>* so = a.smain + (long long)l * main_cpx(g) + ((long long)j * nblk + z) * p.ny * p.mx;
+  const cpx<T>* no = a.snyq + (long long)l * nyq_cpx(g) + ((long long)j * nblk + z) * p.ny;
   PVec<T> sp[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -611,7 +659,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves<
       const int e = q * CV;
       const int ky = p.div_mx(e);
       const int kx = e - ky * p.mx;
-      cpx<T>* row = s.buf + s.py[ky] * p.pitch;
+      cpx<T>* row = s.buf + (P::kY ? s.py[ky] : ky) * p.pitch;
       cpx<T> o[CV];
 #pragma unroll
       for (int i = 0; i < CV; ++i) o[i] = cpx<T>{sp[k].v[2 * i], sp[k].v[2 * i + 1]};
@@ -625,7 +673,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(plane_waves<
     }
   }
   __syncthreads();
-  plane_fft<1, false, T, NT>(s.buf, p, s.twy);
+  if constexpr (P::kY) plane_fft<1, false, T, NT>(s.buf, p, s.twy);
   // 2Z[k] = 2E + i 2O, 2Z[M-k] = conj(2E) + i conj(2O)
   const int h = p.mx / 2;
   for (int idx = tid; idx < (h + 1) * p.ny; idx += NT) {

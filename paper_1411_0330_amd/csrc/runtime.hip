@@ -189,6 +189,8 @@ struct lsh_ctx {
   // keeps the separate x and y passes.
   bool plane = true;
   PlaneGeo pgeo[2] = {};   // FP32, FP64
+  // x passes over blocks of rows where no plane fits (nvec = 0: none)
+  PlaneGeo rgeo[2] = {};
   int tune[2][NPASS] = {{0, 0, 0, 0}, {0, 0, 0, 0}};  // kernel-shape variant per (FP32/FP64, pass)
   // CG breakdown threshold g (|p.Lp| <= g r.r) for FP32 and FP64 fields:
   // eps times a bound of ||L||_2 (max ||(A - A0)^{-1}|| over the phases plus
@@ -474,7 +476,7 @@ void compute_layout(lsh_ctx* ctx) {
   // partial sums: the largest grid of any reducing kernel, per group
   // (the fused CG step writes the x pass's and the z pass's partials side by side)
   // (the fused CG step's x pass: rows, or one partial per plane and component)
-  long long pmax = std::max(xinv_blocks(ctx->geo, 2), (long long)ctx->geo.nz * c) + zg_blocks_max<float>(ctx->geo);
+  long long pmax = std::max(xinv_blocks(ctx->geo, 2), (long long)ctx->geo.nz * ctx->geo.ny * c) + zg_blocks_max<float>(ctx->geo);
   pmax = std::max(pmax, (F + 1023) / 1024 + 1);
   ctx->pstride = pmax;
   ctx->off.partials = take(sizeof(double) * L * c * pmax);
@@ -908,19 +910,56 @@ PlaneGeo plane_geometry(const Geo& g) {
   return p;
 }
 
+// Which x passes run over blocks of rows, where no plane pass applies (nvec 1,
+// or 2 for the small blocks; row lengths of k_plane.hip).
+template <typename T>
+PlaneGeo rows_geometry(const Geo& g) {
+  PlaneGeo p{};
+  p.nx = g.nx;
+  p.ny = g.nz * g.ny;
+  p.mx = g.mx;
+  if (!row_length(g.nx)) return p;
+  const bool small = rows_small(g, rows_per_block<T>(g.nx, false));
+  if (p.ny % rows_per_block<T>(g.nx, small) == 0) p.nvec = small ? 2 : 1;
+  return p;
+}
+// Lengths 3 and 5 times a power of two always (applications 1.1 to 1.5 times as
+// fast as the passes in registers, which run at one or two waves per SIMD
+// there).  Powers of two: the conjugate-gradient passes below 64 MB of field per
+// load (512 x 512 FP64: 24.4 and 23.4 us a pass in registers, 15.1 and 13.4
+// here; streaming from HBM both run at the copy rate, 256^3 elastic FP64 forward
+// 1.50 ms in registers, 1.58 here) except elastic FP64 ones, whose row blocks read
+// the trace's fields again (solves 0.91 to 1.02 times as fast), and 64-point
+// scalar FP32 ones (0.96 to 1.04), and the other passes of scalar FP64 fields
+// below that, 16 MB in 2D (128 x 128: 1.17 times, 1024 x 1024 x 2 loads 0.93
+// times; FP32 below 256 points 0.9 to 0.95 times, elastic FP64 0.82 to 1.08).
+template <typename T>
+bool rows_use(const lsh_ctx* ctx, bool cg) {
+  const Geo& g = ctx->geo;
+  if (odd_part(g.nx) > 1) return true;
+  const double bytes = (double)field_elems(g) * sizeof(T);
+  if (cg) return bytes < 64e6 && (sizeof(T) == 8 ? g.c < 6 : g.c == 6 || g.nx >= 128);
+  return sizeof(T) == 8 && g.c < 6 && bytes < (g.c == 2 ? 16e6 : 64e6);
+}
+
 bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // Whether the x and y passes of this context run as plane passes.
 template <typename T>
-const PlaneGeo* plane_of(lsh_ctx* ctx) {
+const PlaneGeo* plane_of(lsh_ctx* ctx, bool cg) {
   const PlaneGeo& p = ctx->pgeo[sizeof(T) == 8 ? 1 : 0];
-  return (ctx->plane && p.nvec > 0) ? &p : nullptr;
+  if (!ctx->plane) return nullptr;
+  if (p.nvec > 0) return &p;
+  const PlaneGeo& r = ctx->rgeo[sizeof(T) == 8 ? 1 : 0];
+  return r.nvec > 0 && rows_use<T>(ctx, cg) ? &r : nullptr;
 }
+// whether pg is a geometry of planes (their y transform included), not of row blocks
+bool with_y(const lsh_ctx* ctx, const PlaneGeo* pg) { return pg == &ctx->pgeo[0] || pg == &ctx->pgeo[1]; }
 // Forward in mode xmode: the CG mode needs the local term in its short form.
 template <typename T>
 const PlaneGeo* plane_fwd(lsh_ctx* ctx, int xmode, const void* src) {
   if (xmode == XF_CG && !ctx->iso) return nullptr;
-  return aligned16(src) ? plane_of<T>(ctx) : nullptr;
+  return aligned16(src) ? plane_of<T>(ctx, xmode == XF_CG) : nullptr;
 }
 // Inverse in mode `mode` with field tau and output out: the fixed-point modes
 // couple the components of Gamma tau and keep the separate passes, as do
@@ -929,7 +968,7 @@ template <typename T>
 const PlaneGeo* plane_inv(lsh_ctx* ctx, int mode, const void* tau, const void* out) {
   if (mode == XI_BASIC || mode == XI_EM) return nullptr;
   if (mode != XI_STRAIN && !ctx->iso) return nullptr;
-  return (aligned16(tau) && aligned16(out)) ? plane_of<T>(ctx) : nullptr;
+  return (aligned16(tau) && aligned16(out)) ? plane_of<T>(ctx, mode == XI_CGR) : nullptr;
 }
 
 template <typename T>
@@ -950,6 +989,8 @@ PlaneFwdArgs<T> plane_fwd_args(lsh_ctx* ctx, const PlaneGeo& p, cpx<T>* sm, cpx<
   a.prog = ctx->prog;
   return a;
 }
+
+Geo last_axis(const lsh_ctx* ctx);
 
 // Forward passes on load slots [l0, l0+nload): x (mode), y, z (+Gamma and inverse z), y inverse.
 template <typename T>
@@ -976,12 +1017,15 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
     pa.pout = pdir;
     pa.dsrc = dsrc;
     pa.fold = fold;
-    STCHK(check_launch(ctx, launch_pf<T>(ctx->stream, pa, xmode, nload), "x and y forward"));
+    const int nb = with_y(ctx, pg) ? launch_pf<T>(ctx->stream, pa, xmode, nload)
+                                   : launch_rf<T>(ctx->stream, pa, xmode, nload);
+    STCHK(check_launch(ctx, nb, "x forward"));
   } else {
-    {
-      Scope sc(ctx, kcls<T>(K_XFWD), nl * (xin + spec));
-      STCHK(check_launch(ctx, launch_xfwd<T>(ctx->stream, xa, nload, tv<T>(ctx, PASS_XFWD)), "x forward"));
-    }
+    Scope sc(ctx, kcls<T>(K_XFWD), nl * (xin + spec));
+    STCHK(check_launch(ctx, launch_xfwd<T>(ctx->stream, xa, nload, tv<T>(ctx, PASS_XFWD)), "x forward"));
+  }
+  const bool flat = ctx->dim == 2;
+  if (!flat && (!pg || !with_y(ctx, pg))) {
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = sp ? launch_y_paired<T>(ctx->stream, g, -1, sm, sp, sn, Sel<T>::tw(ctx, 1), st, nload,
                                            tv<T>(ctx, PASS_Y))
@@ -994,11 +1038,11 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
                     Sel<T>::gtab(ctx), Sel<T>::gst(ctx)};
     const int nb = sp ? launch_zg_paired<T>(ctx->stream, g, ctx->gp, tb, sp, sn, Sel<T>::tw(ctx, 2), st, nload,
                                             nullptr, 0)
-                      : launch_zg<T>(ctx->stream, g, ctx->gp, tb, gamma ? Z_GAMMA : Z_FWD, sm, sn, Sel<T>::tw(ctx, 2),
-                                     st, nload, tv<T>(ctx, PASS_ZG));
+                      : launch_zg<T>(ctx->stream, last_axis(ctx), ctx->gp, tb, gamma ? Z_GAMMA : Z_FWD, sm, sn,
+                                     Sel<T>::tw(ctx, flat ? 1 : 2), st, nload, tv<T>(ctx, PASS_ZG));
     STCHK(check_launch(ctx, nb, "z/Green"));
   }
-  if (gamma && !skip_yinv) {
+  if (gamma && !flat && !skip_yinv) {
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = sp ? launch_y_paired<T>(ctx->stream, g, 1, sm, sp, sn, Sel<T>::tw(ctx, 1), st, nload,
                                            tv<T>(ctx, PASS_Y))
@@ -1054,13 +1098,24 @@ lsh_status inverse_x(lsh_ctx* ctx, int l0, int nload, int mode, const T* tau, T*
   if (pg) {
     PlaneInvArgs<T> pa{g, *pg, a.smain, a.snyq, a.twx, Sel<T>::tw(ctx, 1), tau, out, rin, rout, a.ptab, a.phase,
                        a.vcoef, a.loads, st, partials, a.pstride, ctx->nphase, a.scale};
-    nb = launch_pi<T>(ctx->stream, pa, mode, nload);
+    nb = with_y(ctx, pg) ? launch_pi<T>(ctx->stream, pa, mode, nload) : launch_ri<T>(ctx->stream, pa, mode, nload);
   } else {
     nb = launch_xinv<T>(ctx->stream, a, nload, tv<T>(ctx, PASS_XINV));
   }
   STCHK(check_launch(ctx, nb, "x inverse"));
   if (nparts) *nparts = nb;
   return LSH_OK;
+}
+
+// 2D grids: y is the last axis, so its transforms and the Green operator are
+// one pass, the z pass of the grid seen as nx x 1 x ny (the same memory layout).
+Geo last_axis(const lsh_ctx* ctx) {
+  Geo g = ctx->geo;
+  if (ctx->dim == 2) {
+    g.nz = g.ny;
+    g.ny = 1;
+  }
+  return g;
 }
 
 // One whole application on load slots [l0, l0+nload): the forward passes of
@@ -1071,7 +1126,7 @@ lsh_status operator_pass(lsh_ctx* ctx, int l0, int nload, int xmode, const T* sr
                          const LoadState* st, int mode, const T* tau, T* out, float* rout, double* partials,
                          int* nparts, const IrxFold& fold = IrxFold{}) {
   const PlaneGeo* pg = paired_shape<T>(ctx) ? nullptr : plane_inv<T>(ctx, mode, tau, out);
-  STCHK(forward_part<T>(ctx, l0, nload, xmode, src, pdir, nullptr, dsrc, st, true, fold, pg != nullptr));
+  STCHK(forward_part<T>(ctx, l0, nload, xmode, src, pdir, nullptr, dsrc, st, true, fold, pg && with_y(ctx, pg)));
   return inverse_x<T>(ctx, l0, nload, mode, tau, out, rout, st, partials, nparts, nullptr, false, pg);
 }
 
@@ -1118,14 +1173,17 @@ lsh_status cg_fused_step(lsh_ctx* ctx, int l0, int nload, T* x, T* r, const T* p
     pa.pout = pout;
     pa.x = x;
     pa.partials = parts;
-    nbx = launch_pf<T>(ctx->stream, pa, XF_CG, nload);
-    STCHK(check_launch(ctx, nbx, "x and y forward (CG)"));
+    nbx = with_y(ctx, pg) ? launch_pf<T>(ctx->stream, pa, XF_CG, nload) : launch_rf<T>(ctx->stream, pa, XF_CG, nload);
+    STCHK(check_launch(ctx, nbx, "x forward (CG)"));
   } else {
-    {
-      Scope sc(ctx, kcls<T>(K_XFWD), nl * (fields * cvs + spec + mat));
-      nbx = launch_xfwdc<T>(ctx->stream, xa, nload);
-      STCHK(check_launch(ctx, nbx, "x forward (CG)"));
-    }
+    Scope sc(ctx, kcls<T>(K_XFWD), nl * (fields * cvs + spec + mat));
+    nbx = launch_xfwdc<T>(ctx->stream, xa, nload);
+    STCHK(check_launch(ctx, nbx, "x forward (CG)"));
+  }
+  // the y transforms belong to the plane passes, or (2D) to the Green pass
+  const bool flat = ctx->dim == 2;
+  const bool py = flat || (pg && with_y(ctx, pg));
+  if (!py) {
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = pr ? launch_y_paired_inplace<T>(ctx->stream, g, -1, sm, sn, Sel<T>::tw(ctx, 1), st, nload,
                                                    tv<T>(ctx, PASS_Y))
@@ -1138,12 +1196,12 @@ lsh_status cg_fused_step(lsh_ctx* ctx, int l0, int nload, T* x, T* r, const T* p
                     Sel<T>::gtab(ctx), Sel<T>::gst(ctx)};
     nbz = pr ? launch_zg_paired<T>(ctx->stream, g, ctx->gp, tb, sm, sn, Sel<T>::tw(ctx, 2), st, nload, parts + nbx,
                                    (int)ctx->pstride)
-             : launch_zg<T>(ctx->stream, g, ctx->gp, tb, Z_GAMMA, sm, sn, Sel<T>::tw(ctx, 2), st, nload,
-                            tv<T>(ctx, PASS_ZG), parts + nbx, (int)ctx->pstride);
+             : launch_zg<T>(ctx->stream, last_axis(ctx), ctx->gp, tb, Z_GAMMA, sm, sn, Sel<T>::tw(ctx, flat ? 1 : 2), st,
+                            nload, tv<T>(ctx, PASS_ZG), parts + nbx, (int)ctx->pstride);
     STCHK(check_launch(ctx, nbz, "z/Green"));
   }
   if (scalars) STCHK(scal(ctx, SC_ALPHA, nload, nbx + nbz, st, ctx->bd_guard[sizeof(T) == 8 ? 1 : 0], l0, par));
-  if (!pg) {
+  if (!py) {
     Scope sc(ctx, kcls<T>(K_Y), nl * 2.0 * spec);
     const int nb = pr ? launch_y_paired_inplace<T>(ctx->stream, g, 1, sm, sn, Sel<T>::tw(ctx, 1), st, nload,
                                                    tv<T>(ctx, PASS_Y))
@@ -1864,6 +1922,8 @@ lsh_status lsh_create(lsh_ctx** out, int dim, const int64_t* n, int physics, int
   tune_from_env(ctx);
   ctx->pgeo[0] = plane_geometry<float>(ctx->geo);
   ctx->pgeo[1] = plane_geometry<double>(ctx->geo);
+  ctx->rgeo[0] = rows_geometry<float>(ctx->geo);
+  ctx->rgeo[1] = rows_geometry<double>(ctx->geo);
   *out = ctx;
   return LSH_OK;
 }
@@ -2663,9 +2723,10 @@ lsh_status lsh_autotune(lsh_ctx* ctx, int nload, const char* cache_path, int32_t
       if (!pass_has_variants(ctx, pass)) continue;
       // x and y run as plane passes, which have one shape
       const bool paired = !fp64 && paired_shape<float>(ctx);
-      const bool planes = fp64 ? plane_inv<double>(ctx, XI_APPLY, nullptr, nullptr) != nullptr
-                               : plane_inv<float>(ctx, XI_APPLY, nullptr, nullptr) != nullptr;
-      if (planes && !paired && pass != PASS_ZG) continue;
+      const int mode = fp64 && ctx->precision == LSH_MIXED ? XI_IRRES : XI_CGR;
+      const PlaneGeo* pg = fp64 ? plane_inv<double>(ctx, mode, nullptr, nullptr)
+                                : plane_inv<float>(ctx, mode, nullptr, nullptr);
+      if (pg && !paired && pass != PASS_ZG && (pass != PASS_Y || with_y(ctx, pg))) continue;
       // the fused CG x pass has one shape (CG fields: FP32 of a mixed context, FP64 of an FP64 one)
       if (pass == PASS_XFWD && ctx->cg_fused && (!fp64 || ctx->precision != LSH_MIXED)) continue;
       const int cls = pass_class(pass, fp64);

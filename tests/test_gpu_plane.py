@@ -75,3 +75,45 @@ def test_plane_solve_equals_separate_passes(lsh, monkeypatch, shape, physics, pr
     # the same recurrences up to rounding; a step more or less moves the result by the tolerance
     tol = 1e-8 if precision == "fp64" else 1e-4
     assert rel_max_err(a1, a0) <= tol and rel_max_err(t1, t0) <= tol and rel_max_err(e1, e0) <= tol
+
+
+@pytest.mark.parametrize("shape", [(2, 4), (4, 16), (48, 64), (80, 48), (160, 96), (16, 128), (128, 80), (96, 160),
+                                   (64, 192), (32, 256), (256, 16), (16, 512), (512, 8), (4, 1024), (1024, 16)])
+@pytest.mark.parametrize("green", ["filtered", "truncated", "fd"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_2d_operator_matches_oracle(lsh, shape, green, dtype):
+    # y transforms and the Green operator in one pass; x over blocks of rows
+    ph = I.random_phases(shape, 2, seed=2)
+    moduli = np.stack([I.scalar_isotropic(1.0, 2), I.scalar_isotropic(10.0, 2)])
+    A0_ = I.scalar_isotropic(0.5, 2)
+    pb = problem(ph, moduli, A0_, "scalar", green)
+    ctx = context(lsh, ph, moduli, A0_, "scalar", green, "mixed" if dtype == "f32" else "fp64", 2)
+    tau = I.random_field(shape, 2, 2, seed=7)
+    out = ctx.apply(to_dev(tau, dtype)).cpu().numpy()
+    for l in range(2):
+        assert rel_max_err(out[l], op.apply(pb, tau[l])) <= (1e-12 if dtype == "f64" else 1e-5)
+
+
+@pytest.mark.parametrize("shape", [(2, 16, 48), (4, 64, 80), (2, 32, 192), (4, 64, 256), (2, 16, 512), (2, 8, 1024),
+                                   (16, 256, 96), (16, 192, 160), (8, 128, 128), (32, 256, 128),
+                                   (64, 128), (128, 256), (32, 512), (16, 1024), (96, 192)])
+@pytest.mark.parametrize("physics,precision", [("scalar", "mixed"), ("scalar", "fp64"), ("elastic", "mixed"),
+                                               ("elastic", "fp64")])
+def test_row_blocks_equal_the_passes_in_registers(lsh, monkeypatch, shape, physics, precision):
+    if len(shape) == 2 and physics == "elastic":
+        pytest.skip("elasticity is three-dimensional")
+    d = len(shape)
+    ph = I.random_phases(shape, 2, seed=4)
+    moduli = ELAS[:2] if physics == "elastic" else np.stack([I.scalar_isotropic(a, d) for a in (1.0, 10.0)])
+    ref = A0["elastic"] if physics == "elastic" else I.scalar_isotropic(0.5, d)
+    got = []
+    for on in ("1", "0"):
+        monkeypatch.setenv("LSH_PLANE", on)
+        ctx = context(lsh, ph, moduli, ref, physics, "filtered", precision, 2)
+        rep = ctx.solve(np.eye(ctx.c)[:2], "cg", tol=1e-10 if precision == "fp64" else 1e-6, maxit=2000)
+        got.append((rep["iterations"], ctx.effective(), ctx.field(1, "tau").cpu().numpy(),
+                    ctx.field(0, "strain").cpu().numpy()))
+    (i1, a1, t1, e1), (i0, a0, t0, e0) = got
+    assert max(abs(x - y) for x, y in zip(i1, i0)) <= 1
+    tol = 1e-8 if precision == "fp64" else 1e-4
+    assert rel_max_err(a1, a0) <= tol and rel_max_err(t1, t0) <= tol and rel_max_err(e1, e0) <= tol
