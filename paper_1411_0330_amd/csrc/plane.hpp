@@ -123,6 +123,11 @@ template <typename T> constexpr int rows_per_block(int n, bool small) {
   return small ? (r >= 4 ? r / 4 : 1) : r;
 }
 inline bool rows_small(const Geo& g, int rb) { return (long long)g.nz * g.ny / rb * g.c < 256; }
+// workgroups per load
+template <typename T> inline long long row_blocks(const Geo& g) {
+  if (!row_length(g.nx)) return 0;
+  return (long long)g.nz * g.ny * g.c / rows_per_block<T>(g.nx, rows_small(g, rows_per_block<T>(g.nx, false)));
+}
 
 template <typename T, int N> using PlaneSq = PlaneFix<T, N, N, true>;
 

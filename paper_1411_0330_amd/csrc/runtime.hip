@@ -475,8 +475,10 @@ void compute_layout(lsh_ctx* ctx) {
   ctx->h_guess.assign(L, 0);
   // partial sums: the largest grid of any reducing kernel, per group
   // (the fused CG step writes the x pass's and the z pass's partials side by side)
-  // (the fused CG step's x pass: rows, or one partial per plane and component)
-  long long pmax = std::max(xinv_blocks(ctx->geo, 2), (long long)ctx->geo.nz * ctx->geo.ny * c) + zg_blocks_max<float>(ctx->geo);
+  // (the fused CG step's x pass: rows, or one partial per component and plane or row block)
+  long long xmax = std::max(xinv_blocks(ctx->geo, 2), (long long)ctx->geo.nz * c);
+  xmax = std::max(xmax, std::max(row_blocks<float>(ctx->geo), row_blocks<double>(ctx->geo)));
+  long long pmax = xmax + zg_blocks_max<float>(ctx->geo);
   pmax = std::max(pmax, (F + 1023) / 1024 + 1);
   ctx->pstride = pmax;
   ctx->off.partials = take(sizeof(double) * L * c * pmax);
