@@ -4,12 +4,18 @@
 
 namespace lsh {
 
-// 2D scalar grids have few registers per point: a 512-thread workgroup takes
-// the rows of a 64^2 grid in one sweep; 3D grids use 256 threads
+// Threads by the radix-8 butterflies of a sweep (W).  512 is the most: with
+// 1024 the fields in registers spill (64^2 FP64 17 -> 22 us an iteration, 16^3
+// FP64 34 -> 43; FP32 within 3%).  From 96 butterflies 256 threads (32^2 FP64
+// 19 us with 128 threads, 8.3 with 256), below it 128.
 template <typename T, int NX, int NY, int NZ, int C>
 static int tiny_inst(hipStream_t s, const TinyArgs<T>& a, int nload) {
-  constexpr int NT = (NZ == 1) ? 512 : 256;
-  hipLaunchKernelGGL((k_tiny_cg<T, NX, NY, NZ, C, NT>), dim3(nload), dim3(NT), 0, s, a);
+  constexpr int W = C * NX * NY * NZ / 16;
+  constexpr int NT = W >= 512 ? 512 : W >= 96 ? 256 : 128;
+  if ((a.vcoef == nullptr && a.iso == 0) || a.gp.variant == kGreenFD)
+    hipLaunchKernelGGL((k_tiny_cg<T, NX, NY, NZ, C, NT, true>), dim3(nload), dim3(NT), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_tiny_cg<T, NX, NY, NZ, C, NT, false>), dim3(nload), dim3(NT), 0, s, a);
   return nload;
 }
 

@@ -1449,11 +1449,7 @@ lsh_status cg_loop(lsh_ctx* ctx, int nload, T* x, T* r, T* p, T* pb, LoadState* 
     ta.hist = hist_ref(ctx, 0, (sizeof(T) == 4 && ctx->precision == LSH_MIXED) ? 1 : 0);
     ta.x = x;
     ta.r = r;
-    ta.p = p;
-    ta.sm = Sel<T>::sm(ctx);
-    ta.sn = Sel<T>::sn(ctx);
     for (int a = 0; a < 3; ++a) ta.tw[a] = Sel<T>::tw(ctx, a);
-    ta.nphase = ctx->nphase;
     ta.iso = ctx->iso;
     ta.ptab = Sel<T>::ptab(ctx);
     ta.phase = ctx->ptr<uint8_t>(ctx->off.phase);

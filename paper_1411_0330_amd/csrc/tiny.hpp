@@ -1,17 +1,32 @@
 // Persistent conjugate gradients for small grids: one workgroup per load runs
-// every iteration of its load in a single launch.  Each iteration is the fused
-// CG step of the multi-kernel path -- x rows (p = r + beta p, x += alpha p of
-// the previous step, p.(A - A0)^{-1} p, R2C), y pencils, the last axis with the
-// Green operator and p.Gamma p (Parseval), the inverse y pencils and the
-// x-inverse rows with r -= alpha Lp and ||r||^2 -- with the passes separated by
-// workgroup barriers instead of kernel boundaries.  Fields and spectra stay in
-// the workspace (cache resident at these sizes); scalars live in registers of
-// every thread, from LDS-broadcast reductions in a fixed order.  The loop ends
-// at convergence, breakdown, non-finite values or maxit, the same in every
-// thread of the workgroup, so no workgroup waits on another.
+// every iteration of its load in a single launch, on chip.  The residual and
+// the direction stay in registers (voxel pairs of a thread, every component),
+// the spectrum and the local coefficients in LDS, the operator matrices of a
+// thread's wave-vectors in registers; the solution (registers in 2D, else the
+// cache-resident workspace) is all that an iteration touches in memory.
+//
+// An iteration is the fused CG step: p = r + beta p with its local form, x, y
+// (and z) transforms in place in LDS (plane.hpp: decimation in frequency, then
+// in time, one butterfly per thread and step, lanes along rows or columns),
+// the Green operator with p.Gamma p (Parseval), the way back, r -= alpha Lp
+// with ||r||^2.  It is bounded by LDS traffic and the latency of its 12 (2D) to
+// 16 (3D) barrier-separated sweeps over the spectrum; the loop that it replaced
+// passed through memory between them.  One iteration of two loads, before and
+// now: FP64 64^2 34 and 15.5 us, 32^2 22 and 8.3, 8^2 18 and 5.5, scalar 8^3 24
+// and 7.6, scalar 16^3 81 and 34 (40 with one kernel per pass), elastic 8^3 51
+// and 8.5; FP32 within the mixed solve 30 and 15 (64^2), 62 and 25 (16^3).
+//
+// Column 0 of the spectrum carries the kx = 0 values and, as its imaginary part
+// before the y transform, the kx = nx/2 ones; the Green step takes its
+// wave-vectors k and -k together and separates the two by symmetry.  Scalars
+// live in registers of every thread, from LDS reductions in a fixed order.  The
+// loop ends at convergence, breakdown, non-finite values or maxit, the same in
+// every thread of the workgroup, so no workgroup waits on another.
 #pragma once
 
-#include "kernels.hpp"
+#include <limits>
+
+#include "plane.hpp"
 
 namespace lsh {
 
@@ -21,12 +36,9 @@ struct TinyArgs {
   GreenParams gp;
   GreenTabs<T> tb;
   T* x;
-  T* r;
-  T* p;
-  cpx<T>* sm;
-  cpx<T>* sn;
+  const T* r;     // initial residual
   const cpx<T>* tw[3];
-  int nphase, iso;
+  int iso;
   const T* ptab;
   const uint8_t* phase;
   const T* vcoef;
@@ -36,15 +48,28 @@ struct TinyArgs {
   HistRef hist;   // residual history (see hist_push)
 };
 
-// workgroup sum of one double, returned to every thread (fixed order)
+// v plus the value that the DPP move brings, zero where it brings none
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWMASK, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWMASK, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+// Workgroup sum of one double, returned to every thread (fixed order).  Lanes
+// add by DPP moves: a serial chain of cross-lane LDS permutes was 1 us a sum.
 template <int NT>
 __device__ __forceinline__ double block_allsum(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) red[w] = v;
+  if (lane == 63) red[w] = v;
   __syncthreads();
   double s = 0.0;
 #pragma unroll
@@ -52,28 +77,163 @@ __device__ __forceinline__ double block_allsum(double v, double* red) {
   return s;
 }
 
-template <typename T, int NX, int NY, int NZ, int C, int NT>
+// Spectrum of a small grid in LDS: row (j, z, y) of pitch mx | 1.
+template <int NX, int NY, int NZ, int C>
+struct TinyGrid {
+  static constexpr int MX = NX / 2, PITCH = MX | 1, ROWS = NY * NZ, NV = NX * ROWS;
+  static constexpr PlaneAxis AX = make_axis(MX, 8), AY = make_axis(NY, 8), AZ = make_axis(NZ, 8);
+  static constexpr PlaneAxis axis(int a) { return a == 0 ? AX : a == 1 ? AY : AZ; }
+};
+
+// One stage of the transforms along axis A of every component: up to U
+// butterflies of a thread at once, all their loads before the first store.
+template <int R, int DIR, int A, typename T, int NT, typename G, int C>
+__device__ __forceinline__ void tiny_stage(cpx<T>* buf, const int L, const int sl, const cpx<T>* tw) {
+  constexpr int n = G::axis(A).n;
+  constexpr int NYv = G::AY.n, NZv = G::AZ.n;
+  constexpr int es = A == 0 ? 1 : A == 1 ? G::PITCH : NYv * G::PITCH;
+  constexpr int nline = A == 0 ? C * G::ROWS : A == 1 ? C * NZv * G::MX : C * NYv * G::MX;
+  constexpr int nb = nline * (n / R);
+  constexpr int NB = (nb + NT - 1) / NT;
+  constexpr int LIM = sizeof(T) == 4 ? 16 : 8;
+  constexpr int U = NB * R <= LIM ? NB : R < LIM ? LIM / R : 1;
+  const int S = 1 << sl;
+  const int ts = (n / L) * (A == 0 ? 2 : 1);
+#pragma unroll 1
+  for (int g = 0; g < NB; g += U) {
+    cpx<T> u[U][R];
+    cpx<T>* p[U];
+    int tj[U];
+    bool on[U];
+    static_for<0, U>([&](auto q_) {
+      constexpr int q = decltype(q_)::value;
+      const int idx = (g + q) * NT + (int)threadIdx.x;
+      on[q] = nb % (NT * U) == 0 || idx < nb;
+      const int b = idx / nline, line = idx - b * nline;
+      int base;
+      if constexpr (A == 0) {
+        base = line * G::PITCH;
+      } else if constexpr (A == 1) {
+        const int s = line / G::MX;
+        base = s * NYv * G::PITCH + (line - s * G::MX);
+      } else {
+        const int r = line / G::MX, j = r / NYv;
+        base = (j * NZv * NYv + (r - j * NYv)) * G::PITCH + (line - r * G::MX);
+      }
+      const int j = b & (S - 1), blk = b >> sl;
+      tj[q] = j * ts;
+      p[q] = buf + base + (blk * L + j) * es;
+      if (on[q]) static_for<0, R>([&](auto r_) { u[q][decltype(r_)::value] = p[q][decltype(r_)::value * S * es]; });
+    });
+    static_for<0, U>([&](auto q_) {
+      constexpr int q = decltype(q_)::value;
+      if (on[q]) {
+        if (DIR > 0 && S > 1) {
+          static_for<1, R>([&](auto r_) {
+            constexpr int r = decltype(r_)::value;
+            u[q][r] = cmulc(u[q][r], tw[r * tj[q]]);
+          });
+        }
+        dft<R, DIR>(u[q]);
+        if (DIR < 0 && S > 1) {
+          static_for<1, R>([&](auto r_) {
+            constexpr int r = decltype(r_)::value;
+            u[q][r] = cmul(u[q][r], tw[r * tj[q]]);
+          });
+        }
+        static_for<0, R>([&](auto r_) { p[q][decltype(r_)::value * S * es] = u[q][decltype(r_)::value]; });
+      }
+    });
+  }
+}
+
+template <int DIR, int A, typename T, int NT, typename G, int C>
+__device__ __forceinline__ void tiny_fft(cpx<T>* buf, const cpx<T>* tw) {
+  constexpr PlaneAxis ax = G::axis(A);
+  static_for<0, ax.ns>([&](auto i_) {
+    constexpr int i = decltype(i_)::value;
+    constexpr PlaneAxis a = G::axis(A);
+    constexpr int s = DIR < 0 ? i : a.ns - 1 - i;
+    tiny_stage<a.r[s], DIR, A, T, NT, G, C>(buf, a.l[s], a.sl[s], tw);
+    __syncthreads();
+  });
+}
+
+// LDS position of a frequency along axis A
+template <int A, typename G>
+__device__ __forceinline__ int tiny_pos(int k) {
+  constexpr PlaneAxis a = G::axis(A);
+  int pos = 0;
+  static_for<0, a.ns>([&](auto s_) {
+    constexpr int s = decltype(s_)::value;
+    constexpr PlaneAxis b = G::axis(A);
+    pos += (k % b.r[s]) << b.sl[s];
+    k /= b.r[s];
+  });
+  return pos;
+}
+
+// The real-split step of every row: f(row[k], row[M-k], W^k) for k = 1..H (at
+// k = H = M/2 the two are one element, written as row[k] last), sum and
+// difference in column 0.
+template <typename T, int NT, int H, int NROW, typename F>
+__device__ __forceinline__ void tiny_rows(cpx<T>* buf, const int pitch, const uint16_t* px, const int M,
+                                          const cpx<T>* tw, F f) {
+  constexpr int N = H * NROW, NB = (N + NT - 1) / NT;
+  constexpr int LIM = sizeof(T) == 4 ? 4 : 2, U = NB < LIM ? NB : LIM;
+  if ((int)threadIdx.x < NROW) {
+    for (int i = threadIdx.x; i < NROW; i += NT) {
+      const cpx<T> z = buf[i * pitch];
+      buf[i * pitch] = cpx<T>{z.x + z.y, z.x - z.y};
+    }
+  }
+#pragma unroll 1
+  for (int g = 0; g < NB; g += U) {
+    cpx<T> z[U], zm[U], w[U];
+    int ia[U], ib[U];
+    static_for<0, U>([&](auto q_) {
+      constexpr int q = decltype(q_)::value;
+      const int idx = (g + q) * NT + (int)threadIdx.x;
+      if (N % (NT * U) == 0 || idx < N) {
+        const int k = 1 + idx / NROW, row = (idx % NROW) * pitch;
+        ia[q] = row + px[k];
+        ib[q] = row + px[M - k];
+        z[q] = buf[ia[q]];
+        zm[q] = buf[ib[q]];
+        w[q] = tw[k];
+      }
+    });
+    static_for<0, U>([&](auto q_) {
+      constexpr int q = decltype(q_)::value;
+      const int idx = (g + q) * NT + (int)threadIdx.x;
+      if (N % (NT * U) == 0 || idx < N) {
+        f(z[q], zm[q], w[q]);
+        buf[ib[q]] = zm[q];
+        buf[ia[q]] = z[q];
+      }
+    });
+  }
+}
+
+// GEN: with phases that need full matrices, or the finite-difference operator
+template <typename T, int NX, int NY, int NZ, int C, int NT, bool GEN>
 __global__ __launch_bounds__(NT) void k_tiny_cg(const TinyArgs<T> a) {
-  constexpr int MX = NX / 2;
-  constexpr int PR = MX < 4 ? MX : 4;                 // row passes
-  constexpr int TR = MX / PR;
-  constexpr int SLOTS = NT / TR;
-  constexpr int ROWS = NY * NZ;
-  constexpr int ROW_IT = (ROWS + SLOTS - 1) / SLOTS;
-  constexpr int PY = NY < 4 ? NY : 4;                 // y pencils
-  constexpr int TY = NY / PY;
-  constexpr int PENY = NT / TY;
-  constexpr int PZ = NZ < 4 ? NZ : 4;                 // z pencils (3D)
-  constexpr int TZ = NZ / PZ;
-  constexpr int PENZ = NT / TZ;
+  using G = TinyGrid<NX, NY, NZ, C>;
+  constexpr int MX = G::MX, PITCH = G::PITCH, ROWS = G::ROWS, H = MX / 2;
+  constexpr int VP = (MX * ROWS + NT - 1) / NT;              // voxel pairs per thread
+  constexpr int MT = ((MX - 1) * ROWS + NT - 1) / NT;        // wave-vectors with 0 < kx < nx/2 per thread
+  constexpr int CT = (ROWS + NT - 1) / NT;                   // (ky, kz) of the kx = 0 and nx/2 planes per thread
+  constexpr int NE = C * (C + 1) / 2;
   constexpr int TABW = 2 * C * C + 5;
-  constexpr int B1 = SLOTS * MX, B2 = PENY * NY, B3 = PENZ * NZ;
-  constexpr int BUF = B1 > B2 ? (B1 > B3 ? B1 : B3) : (B2 > B3 ? B2 : B3);
-  __shared__ cpx<T> buf[BUF];
+  constexpr int CST = ROWS * PITCH;                          // LDS stride of a component
+  constexpr bool XREG = C == 2;
+  __shared__ cpx<T> buf[C * CST];
   __shared__ cpx<T> tw0[NX];
   __shared__ cpx<T> tw1[NY];
   __shared__ cpx<T> tw2[NZ];
-  __shared__ T tab[kMaxPhases * TABW];
+  __shared__ T la[G::NV];                 // short form of (A - A0)^{-1}: a, zero outside I0 ...
+  __shared__ T lb[C == 6 ? G::NV : 1];    // ... and b
+  __shared__ uint16_t px[MX];
   __shared__ double red[NT / 64];
 
   const Geo& g = a.g;
@@ -81,240 +241,198 @@ __global__ __launch_bounds__(NT) void k_tiny_cg(const TinyArgs<T> a) {
   const int tid = threadIdx.x;
   LoadState* st = a.st + l;
   if (!st->active) return;
-  for (int i = tid; i < a.nphase * TABW; i += NT) tab[i] = a.ptab[i];
   for (int i = tid; i < NX; i += NT) tw0[i] = a.tw[0][i];
   for (int i = tid; i < NY; i += NT) tw1[i] = a.tw[1][i];
   for (int i = tid; i < NZ; i += NT) tw2[i] = a.tw[2][i];
+  for (int i = tid; i < MX; i += NT) px[i] = (uint16_t)tiny_pos<0, G>(i);
+  const bool vm = a.vcoef != nullptr;
+  const bool full = GEN && !vm && a.iso == 0;    // phases without the short form: matrices from the table
+  for (int i = tid; i < G::NV; i += NT) {
+    if (vm) {
+      la[i] = a.vcoef[i];
+      if constexpr (C == 6) lb[i] = a.vcoef[G::NV + i];
+    } else {
+      const T* t = a.ptab + (int)a.phase[i] * TABW + 2 * C * C;
+      la[i] = full || t[0] == T(0) ? t[0] : t[1] != T(0) ? t[1] : std::numeric_limits<T>::denorm_min();
+      if constexpr (C == 6) lb[i] = t[2];
+    }
+  }
   const long long F = field_elems(g);
   T* x = a.x + (long long)l * F;
-  T* r = a.r + (long long)l * F;
-  T* p = a.p + (long long)l * F;
-  cpx<T>* sm = a.sm + (long long)l * main_cpx(g);
-  cpx<T>* sn = a.sn + (long long)l * nyq_cpx(g);
-  const bool iso = a.iso != 0;
-  const bool vm = a.vcoef != nullptr;
+  const T* r0 = a.r + (long long)l * F;
+
+  // the operator at this thread's wave-vectors (the finite-difference one,
+  // complex, is formed at every application)
+  const bool fd = GEN && a.gp.variant == kGreenFD;
+  T Gm[MT][NE], G0[CT][NE], GN[CT][NE];
+  if (!fd) {
+    static_for<0, MT>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int q = k * NT + tid;
+      if (q < (MX - 1) * ROWS) {
+        const int m = q / (MX - 1), kx = 1 + q % (MX - 1), kz = m / NY, ky = m % NY;
+        const int kk[3] = {kx, ky, kz};
+        green_matrix<T, C>(a.gp, a.tb, kk, (long long)m * MX + kx, Gm[k]);
+      }
+    });
+    static_for<0, CT>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int m = k * NT + tid;
+      if (m < ROWS) {
+        const int kz = m / NY, ky = m % NY;
+        const int k0[3] = {0, ky, kz}, kn[3] = {MX, ky, kz};
+        green_matrix<T, C>(a.gp, a.tb, k0, (long long)m * MX, G0[k]);
+        green_matrix<T, C>(a.gp, a.tb, kn, (long long)ROWS * MX + m, GN[k]);
+      }
+    });
+  }
+
+  cpx<T> r[VP][C], p[VP][C], xr[XREG ? VP : 1][C];
+  static_for<0, VP>([&](auto k_) {
+    constexpr int k = decltype(k_)::value;
+    const int q = k * NT + tid;
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      r[k][j].x = r[k][j].y = p[k][j].x = p[k][j].y = T(0);
+      if (q < MX * ROWS) {
+        const T* rp = r0 + (long long)j * G::NV + 2 * q;
+        r[k][j].x = rp[0];
+        r[k][j].y = rp[1];
+        if constexpr (XREG) {
+          const T* xp = x + (long long)j * G::NV + 2 * q;
+          xr[k][j].x = xp[0];
+          xr[k][j].y = xp[1];
+        }
+      }
+    }
+  });
   const double tol2 = st->tol2;
   double rr = st->rr;
   double alpha = 0.0, beta = 0.0;
-  bool first = true, pend = false;
+  bool first = true;
   int iters = st->iters, status = kStatusOk;
   bool done = false;
   __syncthreads();
 
+  // row j of (A - A0)^{-1} at one voxel, times the field (v) there
+  auto local_row = [&](const int vox, const int j, const T (&v)[C]) -> T {
+    if (full) {
+      const T* M = a.ptab + (int)a.phase[vox] * TABW + j * C;
+      T s = 0;
+#pragma unroll
+      for (int m = 0; m < C; ++m) s += M[m] * v[m];
+      return la[vox] * s;
+    }
+    T s = la[vox] * v[j];
+    if constexpr (C == 6) {
+      if (j < 3) s += lb[vox] * (v[0] + v[1] + v[2]);
+    }
+    return s;
+  };
+
   for (int it = 0; it < a.maxit; ++it) {
     double part = 0.0;
-    // ---------------- x rows: p, x, local form, R2C ----------------
-    {
-      const int slot = tid / TR, t = tid % TR;
-      cpx<T>* lrow = buf + slot * MX;
-      for (int ri = 0; ri < ROW_IT; ++ri) {
-        const int vr = ri * SLOTS + slot;
-        const bool valid = vr < ROWS;
-        const long long vrc = valid ? vr : 0;
-        cpx<T> v[C][PR];
+    // p = r + beta p, its local form, and the rows into LDS
+    static_for<0, VP>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int q = k * NT + tid;
+      if (q < MX * ROWS) {
+        T p0[C], p1[C];
+        const int row = q / MX, n = q % MX;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-          const long long roff = (long long)j * g.nvox + vrc * NX;
-          const cpx<T>* r2 = reinterpret_cast<const cpx<T>*>(r + roff);
-          cpx<T>* p2 = reinterpret_cast<cpx<T>*>(p + roff);
-          cpx<T>* x2 = reinterpret_cast<cpx<T>*>(x + roff);
-#pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            const int n = t + TR * i;
-            cpx<T> pv{0, 0};
-            if (valid) {
-              const cpx<T> rv = r2[n];
-              if (first) {
-                pv = rv;
-              } else {
-                const cpx<T> po = p2[n];
-                if (pend) {
-                  const cpx<T> xo = x2[n];
-                  x2[n] = cpx<T>{xo.x + static_cast<T>(alpha) * po.x, xo.y + static_cast<T>(alpha) * po.y};
-                }
-                pv = cpx<T>{rv.x + static_cast<T>(beta) * po.x, rv.y + static_cast<T>(beta) * po.y};
-              }
-              p2[n] = pv;
-            }
-            v[j][i] = pv;
-          }
+          const T be = static_cast<T>(beta);
+          p0[j] = p[k][j].x = first ? r[k][j].x : r[k][j].x + be * p[k][j].x;
+          p1[j] = p[k][j].y = first ? r[k][j].y : r[k][j].y + be * p[k][j].y;
+          buf[j * CST + row * PITCH + n] = cpx<T>{p0[j], p1[j]};
         }
-        if (valid) {
-#pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            const long long vox = vrc * NX + 2 * (t + TR * i);
-            Loc<T> L0, L1;
-            if (vm) {
-              const cpx<T> ai = *reinterpret_cast<const cpx<T>*>(a.vcoef + vox);
-              const cpx<T> bi = *reinterpret_cast<const cpx<T>*>(a.vcoef + g.nvox + vox);
-              L0 = Loc<T>{nullptr, ai.x != T(0) ? T(1) : T(0), ai.x, bi.x};
-              L1 = Loc<T>{nullptr, ai.y != T(0) ? T(1) : T(0), ai.y, bi.y};
-            } else {
-              const uint16_t ph2 = *reinterpret_cast<const uint16_t*>(a.phase + vox);
-              const T* tb0 = tab + (ph2 & 0xff) * TABW;
-              const T* tb1 = tab + (ph2 >> 8) * TABW;
-              L0 = Loc<T>{tb0, tb0[2 * C * C], T(0), T(0)};
-              L1 = Loc<T>{tb1, tb1[2 * C * C], T(0), T(0)};
-            }
-            T p0[C], p1[C];
-#pragma unroll
-            for (int j = 0; j < C; ++j) {
-              p0[j] = v[j][i].x;
-              p1[j] = v[j][i].y;
-            }
-            part += (double)(L0.in * loc_quad<T, C>(L0, vm, iso, p0)) +
-                    (double)(L1.in * loc_quad<T, C>(L1, vm, iso, p1));
-          }
-        }
-        fft_pencil_multi<MX, PR, -1, T, C>(v, t, lrow, 1, tw0, 2);
+        T q0 = 0, q1 = 0;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-          __syncthreads();
-#pragma unroll
-          for (int i = 0; i < PR; ++i) lrow[t + TR * i] = v[j][i];
-          __syncthreads();
-          const long long row = (long long)j * ROWS + vrc;
-#pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            const int k = t + TR * i;
-            const cpx<T> z = v[j][i];
-            if (k == 0) {
-              if (valid) {
-                sm[row * MX] = cpx<T>{z.x + z.y, T(0)};
-                sn[row] = cpx<T>{z.x - z.y, T(0)};
-              }
-            } else {
-              const cpx<T> zm = lrow[MX - k];
-              const cpx<T> s1 = cpx<T>{z.x + zm.x, z.y - zm.y};
-              const cpx<T> d1 = cpx<T>{z.x - zm.x, z.y + zm.y};
-              const cpx<T> wo = cmul(tw0[k], mul_neg_i(d1));
-              if (valid) sm[row * MX + k] = cpx<T>{T(0.5) * (s1.x + wo.x), T(0.5) * (s1.y + wo.y)};
-            }
-          }
+          q0 += p0[j] * local_row(2 * q, j, p0);
+          q1 += p1[j] * local_row(2 * q + 1, j, p1);
         }
-        __syncthreads();
+        part += (double)q0 + (double)q1;
       }
-    }
-    // ---------------- y pencils (3D: plain forward transforms) ----------------
-    auto y_pass = [&](auto dir_) {
-      constexpr int DIR = decltype(dir_)::value;
-      const int q0 = tid / TY, t = tid % TY;
-      cpx<T>* lp = buf + q0 * NY;
-      constexpr int NPEN = C * NZ * (MX + 1);
-      for (int pb = 0; pb < NPEN; pb += PENY) {
-        const int q = pb + q0;
-        const bool valid = q < NPEN;
-        const int qq = valid ? q : 0;
-        const int j = qq / (NZ * (MX + 1));
-        const int rem = qq % (NZ * (MX + 1));
-        const int kz = rem / (MX + 1), kx = rem % (MX + 1);
-        cpx<T>* base;
-        long long es;
-        if (kx < MX) {
-          base = sm + ((long long)(j * NZ + kz) * NY) * MX + kx;
-          es = MX;
+    });
+    __syncthreads();
+    tiny_fft<-1, 0, T, NT, G, C>(buf, tw0);
+    // X[k] = E + W^k O, X[M-k] = conj(E - W^k O); column 0: (X[0], X[M])
+    tiny_rows<T, NT, H, C * ROWS>(buf, PITCH, px, MX, tw0, [](cpx<T>& z, cpx<T>& zm, const cpx<T> w) {
+      const cpx<T> e = cpx<T>{T(0.5) * (z.x + zm.x), T(0.5) * (z.y - zm.y)};
+      const cpx<T> d = cpx<T>{T(0.5) * (z.x - zm.x), T(0.5) * (z.y + zm.y)};
+      const cpx<T> o = cmul(w, mul_neg_i(d));
+      z = cadd(e, o);
+      zm = cpx<T>{e.x - o.x, o.y - e.y};
+    });
+    __syncthreads();
+    tiny_fft<-1, 1, T, NT, G, C>(buf, tw1);
+    if constexpr (NZ > 1) tiny_fft<-1, 2, T, NT, G, C>(buf, tw2);
+    // Gamma and tau_hat . Gamma tau_hat (weights 2 and, on the kx = 0 and nx/2 planes, 1)
+    double quad = 0.0;
+    static_for<0, MT>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int q = k * NT + tid;
+      if (q < (MX - 1) * ROWS) {
+        const int m = q / (MX - 1), kx = 1 + q % (MX - 1), kz = m / NY, ky = m % NY;
+        cpx<T>* e = buf + (tiny_pos<2, G>(kz) * NY + tiny_pos<1, G>(ky)) * PITCH + px[kx];
+        cpx<T> v[C], w[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) w[j] = v[j] = e[j * CST];
+        if (fd) {
+          const int kk[3] = {kx, ky, kz};
+          green_apply<T, C>(a.gp, a.tb, kk, 0, w);
         } else {
-          base = sn + (long long)(j * NZ + kz) * NY;
-          es = 1;
+          sym_apply<T, C>(Gm[k], w);
         }
-        cpx<T> v[PY];
+        double d = 0.0;
 #pragma unroll
-        for (int i = 0; i < PY; ++i) v[i] = valid ? base[(long long)(t + TY * i) * es] : cpx<T>{0, 0};
-        fft_pencil<NY, PY, DIR, T>(v, t, lp, 1, tw1, 1);
-        if (valid) {
-#pragma unroll
-          for (int i = 0; i < PY; ++i) base[(long long)(t + TY * i) * es] = v[i];
+        for (int j = 0; j < C; ++j) {
+          d += (double)v[j].x * w[j].x + (double)v[j].y * w[j].y;
+          e[j * CST] = w[j];
         }
-        __syncthreads();
+        quad += 2.0 * d;
       }
-    };
-    if constexpr (NZ > 1) y_pass(std::integral_constant<int, -1>{});
-    // ---------------- last axis with the Green operator ----------------
-    {
-      // pencils along z (3D) or y (2D), all C components per thread
-      constexpr int NL = NZ > 1 ? NZ : NY;
-      constexpr int PL = NZ > 1 ? PZ : PY;
-      constexpr int TL = NL / PL;
-      constexpr int PENL = NT / TL;
-      constexpr int NPEN = NZ > 1 ? NY * (MX + 1) : (MX + 1);
-      const cpx<T>* twl = NZ > 1 ? tw2 : tw1;
-      const int q0 = tid / TL, t = tid % TL;
-      cpx<T>* lp = buf + q0 * NL;
-      for (int pb = 0; pb < NPEN; pb += PENL) {
-        const int q = pb + q0;
-        const bool valid = q < NPEN;
-        const int qq = valid ? q : 0;
-        int kx, ky = 0;
-        cpx<T>* base;
-        long long es, cs;
-        if constexpr (NZ > 1) {
-          ky = qq / (MX + 1);
-          kx = qq % (MX + 1);
-          if (kx < MX) {
-            base = sm + (long long)ky * MX + kx;
-            es = (long long)NY * MX;
-            cs = (long long)NZ * NY * MX;
+    });
+    static_for<0, CT>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int m = k * NT + tid;
+      if (m < ROWS) {
+        const int kz = m / NY, ky = m % NY;
+        const int nz_ = kz == 0 ? 0 : NZ - kz, ny_ = ky == 0 ? 0 : NY - ky;
+        const int mm = nz_ * NY + ny_;   // -k
+        if (m <= mm) {
+          cpx<T>* e = buf + (tiny_pos<2, G>(kz) * NY + tiny_pos<1, G>(ky)) * PITCH;
+          cpx<T>* f = buf + (tiny_pos<2, G>(nz_) * NY + tiny_pos<1, G>(ny_)) * PITCH;
+          cpx<T> v0[C], vn[C], w0[C], wn[C];
+#pragma unroll
+          for (int j = 0; j < C; ++j) {
+            const cpx<T> c = e[j * CST], d = f[j * CST];
+            w0[j] = v0[j] = cpx<T>{T(0.5) * (c.x + d.x), T(0.5) * (c.y - d.y)};
+            wn[j] = vn[j] = cpx<T>{T(0.5) * (c.y + d.y), T(0.5) * (d.x - c.x)};
+          }
+          if (fd) {
+            const int k0[3] = {0, ky, kz}, kn[3] = {MX, ky, kz};
+            green_apply<T, C>(a.gp, a.tb, k0, 0, w0);
+            green_apply<T, C>(a.gp, a.tb, kn, 0, wn);
           } else {
-            base = sn + ky;
-            es = NY;
-            cs = (long long)NZ * NY;
+            sym_apply<T, C>(G0[k], w0);
+            sym_apply<T, C>(GN[k], wn);
           }
-        } else {
-          kx = qq;
-          if (kx < MX) {
-            base = sm + kx;
-            es = MX;
-            cs = (long long)NY * MX;
-          } else {
-            base = sn;
-            es = 1;
-            cs = NY;
+          double d = 0.0;
+#pragma unroll
+          for (int j = 0; j < C; ++j) {
+            d += (double)v0[j].x * w0[j].x + (double)v0[j].y * w0[j].y + (double)vn[j].x * wn[j].x +
+                 (double)vn[j].y * wn[j].y;
+            // Y0 + i YN at k, conj(Y0) + i conj(YN) at -k
+            e[j * CST] = cpx<T>{w0[j].x - wn[j].y, w0[j].y + wn[j].x};
+            if (mm != m) f[j * CST] = cpx<T>{w0[j].x + wn[j].y, wn[j].x - w0[j].y};
           }
+          quad += mm != m ? 2.0 * d : d;
         }
-        cpx<T> v[C][PL];
-#pragma unroll
-        for (int j = 0; j < C; ++j)
-#pragma unroll
-          for (int i = 0; i < PL; ++i) v[j][i] = valid ? base[j * cs + (long long)(t + TL * i) * es] : cpx<T>{0, 0};
-        fft_pencil_multi<NL, PL, -1, T, C>(v, t, lp, 1, twl, 1);
-        double quad = 0.0;
-        if (valid) {
-#pragma unroll
-          for (int i = 0; i < PL; ++i) {
-            const int kl = t + TL * i;
-            int k[3];
-            long long tidx;
-            if constexpr (NZ > 1) {
-              k[0] = kx; k[1] = ky; k[2] = kl;
-              tidx = (kx < MX) ? ((long long)kl * NY + ky) * MX + kx
-                               : (long long)NZ * NY * MX + (long long)kl * NY + ky;
-            } else {
-              k[0] = kx; k[1] = kl; k[2] = 0;
-              tidx = (kx < MX) ? (long long)kl * MX + kx : (long long)NY * MX + kl;
-            }
-            cpx<T> w[C];
-#pragma unroll
-            for (int j = 0; j < C; ++j) w[j] = v[j][i];
-            green_apply<T, C>(a.gp, a.tb, k, tidx, w);
-#pragma unroll
-            for (int j = 0; j < C; ++j) {
-              quad += (double)v[j][i].x * w[j].x + (double)v[j][i].y * w[j].y;
-              v[j][i] = w[j];
-            }
-          }
-        }
-        part += quad * ((kx == 0 || kx == MX) ? 1.0 : 2.0) / (double)g.nvox;
-        fft_pencil_multi<NL, PL, 1, T, C>(v, t, lp, 1, twl, 1);
-        if (valid) {
-#pragma unroll
-          for (int j = 0; j < C; ++j)
-#pragma unroll
-            for (int i = 0; i < PL; ++i) base[j * cs + (long long)(t + TL * i) * es] = v[j][i];
-        }
-        __syncthreads();
       }
-    }
-    // ---------------- alpha ----------------
+    });
+    part += quad / (double)G::NV;
     const double pq = block_allsum<NT>(part, red);
     if (!isfinite(pq)) {
       status = kStatusNumeric;
@@ -326,92 +444,69 @@ __global__ __launch_bounds__(NT) void k_tiny_cg(const TinyArgs<T> a) {
     }
     alpha = rr / pq;
     first = false;
-    pend = true;
-    if constexpr (NZ > 1) y_pass(std::integral_constant<int, 1>{});
-    // ---------------- x-inverse rows: r -= alpha L p, ||r||^2 ----------------
+    // the way back (block_allsum's barriers stand between the Green step and this)
+    if constexpr (NZ > 1) tiny_fft<1, 2, T, NT, G, C>(buf, tw2);
+    tiny_fft<1, 1, T, NT, G, C>(buf, tw1);
+    tiny_rows<T, NT, H, C * ROWS>(buf, PITCH, px, MX, tw0, [](cpx<T>& x0, cpx<T>& xm, const cpx<T> w) {
+      const cpx<T> e = cpx<T>{x0.x + xm.x, x0.y - xm.y};
+      const cpx<T> d = cpx<T>{x0.x - xm.x, x0.y + xm.y};
+      const cpx<T> o = cmulc(d, w);
+      x0 = cpx<T>{e.x - o.y, e.y + o.x};
+      xm = cpx<T>{e.x + o.y, o.x - e.y};
+    });
+    __syncthreads();
+    tiny_fft<1, 0, T, NT, G, C>(buf, tw0);
+    // r -= alpha L p on I0, ||r||^2
     part = 0.0;
-    {
-      const int slot = tid / TR, t = tid % TR;
-      cpx<T>* lrow = buf + slot * MX;
-      const T al = static_cast<T>(alpha);
-      const T sc = static_cast<T>(1.0 / (double)g.nvox);
-      for (int ri = 0; ri < ROW_IT; ++ri) {
-        const int vr = ri * SLOTS + slot;
-        const bool valid = vr < ROWS;
-        const long long vrc = valid ? vr : 0;
-        cpx<T> gam[C][PR];
-        cpx<T> nqs[C];
+    const T al = static_cast<T>(alpha);
+    const T sc = static_cast<T>(1.0 / (double)G::NV);
+    static_for<0, VP>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int q = k * NT + tid;
+      if (q < MX * ROWS) {
+        const int row = q / MX, n = q % MX;
+        const T in0 = la[2 * q] != T(0) ? T(1) : T(0), in1 = la[2 * q + 1] != T(0) ? T(1) : T(0);
+        T p0[C], p1[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-          const long long srow = (long long)j * ROWS + vrc;
-#pragma unroll
-          for (int i = 0; i < PR; ++i) gam[j][i] = sm[srow * MX + t + TR * i];
-          nqs[j] = sn[srow];
+          p0[j] = p[k][j].x;
+          p1[j] = p[k][j].y;
         }
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-          __syncthreads();
-#pragma unroll
-          for (int i = 0; i < PR; ++i) lrow[t + TR * i] = gam[j][i];
-          __syncthreads();
-#pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            const int k = t + TR * i;
-            const cpx<T> xk = gam[j][i];
-            const cpx<T> xm = (k == 0) ? nqs[j] : lrow[MX - k];
-            const cpx<T> e = cpx<T>{xk.x + xm.x, xk.y - xm.y};
-            const cpx<T> d = cpx<T>{xk.x - xm.x, xk.y + xm.y};
-            const cpx<T> o = cmulc(d, tw0[k]);
-            gam[j][i] = cadd(e, mul_i(o));
-          }
+          const cpx<T> gv = buf[j * CST + row * PITCH + n];
+          const T q0 = in0 * (local_row(2 * q, j, p0) + gv.x * sc);
+          const T q1 = in1 * (local_row(2 * q + 1, j, p1) + gv.y * sc);
+          r[k][j].x -= al * q0;
+          r[k][j].y -= al * q1;
+          part += (double)r[k][j].x * r[k][j].x + (double)r[k][j].y * r[k][j].y;
         }
-        __syncthreads();
-        fft_pencil_multi<MX, PR, 1, T, C>(gam, t, lrow, 1, tw0, 2);
-        if (valid) {
-#pragma unroll
-          for (int i = 0; i < PR; ++i) {
-            const long long vox = vrc * NX + 2 * (t + TR * i);
-            T t0[C], t1[C];
-#pragma unroll
-            for (int j = 0; j < C; ++j) {
-              const cpx<T> tv = *reinterpret_cast<const cpx<T>*>(p + (long long)j * g.nvox + vox);
-              t0[j] = tv.x;
-              t1[j] = tv.y;
-            }
-            Loc<T> L0, L1;
-            if (vm) {
-              const cpx<T> ai = *reinterpret_cast<const cpx<T>*>(a.vcoef + vox);
-              const cpx<T> bi = *reinterpret_cast<const cpx<T>*>(a.vcoef + g.nvox + vox);
-              L0 = Loc<T>{nullptr, ai.x != T(0) ? T(1) : T(0), ai.x, bi.x};
-              L1 = Loc<T>{nullptr, ai.y != T(0) ? T(1) : T(0), ai.y, bi.y};
-            } else {
-              const uint16_t ph2 = *reinterpret_cast<const uint16_t*>(a.phase + vox);
-              const T* tb0 = tab + (ph2 & 0xff) * TABW;
-              const T* tb1 = tab + (ph2 >> 8) * TABW;
-              L0 = Loc<T>{tb0, tb0[2 * C * C], T(0), T(0)};
-              L1 = Loc<T>{tb1, tb1[2 * C * C], T(0), T(0)};
-            }
-#pragma unroll
-            for (int j = 0; j < C; ++j) {
-              cpx<T>* rp = reinterpret_cast<cpx<T>*>(r + (long long)j * g.nvox + vox);
-              const cpx<T> rv = *rp;
-              const T q0 = L0.in * (loc_row<T, C>(L0, vm, 0, iso, j, t0) + gam[j][i].x * sc);
-              const T q1 = L1.in * (loc_row<T, C>(L1, vm, 0, iso, j, t1) + gam[j][i].y * sc);
-              const cpx<T> rn{rv.x - al * q0, rv.y - al * q1};
-              *rp = rn;
-              part += (double)rn.x * rn.x + (double)rn.y * rn.y;
-            }
-          }
-        }
-        __syncthreads();
       }
-    }
+    });
     const double rr_new = block_allsum<NT>(part, red);
     ++iters;
     if (!isfinite(rr_new)) {
       status = kStatusNumeric;
       break;
     }
+    // x += alpha p
+    static_for<0, VP>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int q = k * NT + tid;
+      if (q < MX * ROWS) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          if constexpr (XREG) {
+            xr[k][j].x += al * p[k][j].x;
+            xr[k][j].y += al * p[k][j].y;
+          } else {
+            cpx<T>* xp = reinterpret_cast<cpx<T>*>(x + (long long)j * G::NV + 2 * q);
+            const cpx<T> xo = *xp;
+            *xp = cpx<T>{xo.x + al * p[k][j].x, xo.y + al * p[k][j].y};
+          }
+        }
+      }
+    });
     beta = rr_new / rr;
     rr = rr_new;
     if (tid == 0) hist_push(a.hist, l, rr / st->bb);
@@ -420,11 +515,20 @@ __global__ __launch_bounds__(NT) void k_tiny_cg(const TinyArgs<T> a) {
       break;
     }
   }
-  // apply the last step's x += alpha p
-  if (pend && status == kStatusOk) {
-    for (long long e = tid; e < F; e += NT) x[e] += static_cast<T>(alpha) * p[e];
+  if constexpr (XREG) {
+    static_for<0, VP>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const int q = k * NT + tid;
+      if (q < MX * ROWS) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          T* xp = x + (long long)j * G::NV + 2 * q;
+          xp[0] = xr[k][j].x;
+          xp[1] = xr[k][j].y;
+        }
+      }
+    });
   }
-  __syncthreads();
   if (tid == 0) {
     st->rr = rr;
     st->res2 = rr;
