@@ -54,9 +54,13 @@ struct HistRef {
   unsigned long long* count;    // [load]
   int level;
 };
-__device__ __forceinline__ void hist_push(const HistRef& h, const int load, const double rel2) {
+__device__ __forceinline__ unsigned long long hist_count(const HistRef& h, const int load) {
+  return h.ring == nullptr ? 0 : h.count[load];
+}
+// i: the load's count, read beforehand
+__device__ __forceinline__ void hist_push(const HistRef& h, const int load, const double rel2,
+                                          const unsigned long long i) {
   if (h.ring == nullptr) return;
-  const unsigned long long i = h.count[load];
   h.count[load] = i + 1;
   double* e = h.ring + ((long long)load * kHistCap + (long long)(i % kHistCap)) * 2;
   e[0] = rel2;
@@ -112,6 +116,24 @@ enum : int { SC_INIT = 0, SC_ALPHA = 1, SC_BETA = 2, SC_BASIC = 3, SC_OUTER = 4,
 
 constexpr int kMaxPhases = 32;
 constexpr int kStatusOk = 0, kStatusBreakdown = -5, kStatusNumeric = -6;
+
+// v plus the value that the DPP move brings, zero where it brings none
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWMASK, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWMASK, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+// Sum over a wave, in lane 63 (fixed order).
+__device__ __forceinline__ double wave_total(double v) {
+  v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+}
 
 // ----------------------------------------------------------------------------
 // workgroup reduction of one double (wave64 shuffles, then LDS), fixed order

@@ -1120,6 +1120,10 @@ Geo last_axis(const lsh_ctx* ctx) {
   return g;
 }
 
+// Threads of a scalar kernel's one workgroup per load: a round of loads each
+// way (192^3 x 6 FP64, 16000 partials: 50 us with 256 threads, one load each).
+int scal_threads(int nparts) { return nparts > 1024 ? 1024 : 256; }
+
 // One whole application on load slots [l0, l0+nload): the forward passes of
 // src (x mode `xmode`), Gamma, and the inverse passes with the epilogue `mode`
 // on the field tau (the field transformed).
@@ -1226,7 +1230,7 @@ lsh_status scal(lsh_ctx* ctx, int mode, int ngroups, int nparts, LoadState* st, 
   // the inner FP32 states of a mixed solve record at level 1, every other state at 0
   const LoadState* sin = ctx->ptr<LoadState>(ctx->off.st_in);
   const int level = (st >= sin && st < sin + ctx->max_loads) ? 1 : 0;
-  hipLaunchKernelGGL(k_scal, dim3(ngroups), dim3(256), 0, ctx->stream, mode,
+  hipLaunchKernelGGL(k_scal, dim3(ngroups), dim3(scal_threads(nparts)), 0, ctx->stream, mode,
                      ctx->ptr<double>(ctx->off.partials) + (long long)l0 * ctx->pstride, (int)ctx->pstride, nparts,
                      st, ctx->ptr<double>(ctx->off.sums) + l0, tol, aux, hist_ref(ctx, l0, level));
   return check_launch(ctx, 0, "scalars");
@@ -1548,7 +1552,7 @@ lsh_status mr_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
     STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, st, XI_CG, v, q, nullptr, parts, &np));
     {
       Scope sc(ctx, K_SCAL);
-      hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(256), 0, ctx->stream, (int)MR_ALPHA, parts, (int)ctx->pstride,
+      hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(scal_threads(np)), 0, ctx->stream, (int)MR_ALPHA, parts, (int)ctx->pstride,
                          np, st, ms, hist_ref(ctx, 0, 0));
       STCHK(check_launch(ctx, 0, "minres alpha"));
     }
@@ -1560,7 +1564,7 @@ lsh_status mr_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
     }
     {
       Scope sc(ctx, K_SCAL);
-      hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(256), 0, ctx->stream, (int)MR_ROT, parts, (int)ctx->pstride,
+      hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(scal_threads(nbe)), 0, ctx->stream, (int)MR_ROT, parts, (int)ctx->pstride,
                          nbe, st, ms, hist_ref(ctx, 0, 0));
       STCHK(check_launch(ctx, 0, "minres rotation"));
     }
@@ -1614,7 +1618,7 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
     STCHK(operator_pass<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, st, XI_CG, v, q, nullptr, parts, &np));
     {
       Scope sc(ctx, K_SCAL);
-      hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(256), 0, ctx->stream, (int)MR_ALPHA, parts, (int)ctx->pstride,
+      hipLaunchKernelGGL(k_mr_scal, dim3(nload), dim3(scal_threads(np)), 0, ctx->stream, (int)MR_ALPHA, parts, (int)ctx->pstride,
                          np, st, ms, hist_ref(ctx, 0, 0));
       STCHK(check_launch(ctx, 0, "symmlq alpha"));
     }
@@ -1626,7 +1630,7 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
     }
     {
       Scope sc(ctx, K_SCAL);
-      hipLaunchKernelGGL(k_sy_scal, dim3(nload), dim3(256), 0, ctx->stream, (int)SY_ROT, parts, (int)ctx->pstride,
+      hipLaunchKernelGGL(k_sy_scal, dim3(nload), dim3(scal_threads(nbe)), 0, ctx->stream, (int)SY_ROT, parts, (int)ctx->pstride,
                          nbe, it + 1 == maxit ? 1 : 0, st, ms, hist_ref(ctx, 0, 0));
       STCHK(check_launch(ctx, 0, "symmlq rotation"));
     }

@@ -88,17 +88,25 @@ static __global__ __launch_bounds__(256) void k_mr_update(const long long F, con
   }
 }
 
+// Sum of the partials of one group, to every thread.  Four independent loads a
+// thread and round: the sum is a chain of memory latencies, not bandwidth.
 __device__ __forceinline__ double group_sum(const double* __restrict__ partials, int pstride, int nparts, int grp,
                                             double* red) {
-  double s = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += 256) s += partials[(long long)grp * pstride + i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  const double* p = partials + (long long)grp * pstride;
+  const int nt = blockDim.x;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < nparts; i += 4 * nt) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i + u * nt < nparts) s[u] += p[i + u * nt];
   }
-  return red[0];
+  const double v = wave_total((s[0] + s[1]) + (s[2] + s[3]));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < (nt >> 6); ++w) t += red[w];
+  return t;
 }
 
 // Scalar steps of MINRES (one workgroup per load).  MR_ROT applies the
@@ -106,16 +114,8 @@ __device__ __forceinline__ double group_sum(const double* __restrict__ partials,
 // beta_{k+1}), forms the next rotation, the step t_k = c_k phi_{k-1} and the
 // residual norm phi_k = s_k phi_{k-1}; the load stops at |phi_k| <= tol ||b||,
 // at beta_{k+1} = 0 (exact solution) or, with gamma2 = 0, on breakdown.
-static __global__ __launch_bounds__(256) void k_mr_scal(const int mode, const double* __restrict__ partials,
-                                                        const int pstride, const int nparts,
-                                                        LoadState* __restrict__ st, MinresState* __restrict__ ms,
-                                                        const HistRef hist) {
-  __shared__ double red[256];
-  const int l = blockIdx.x;
-  const double S = mode == MR_INIT ? 0.0 : group_sum(partials, pstride, nparts, l, red);
-  if (threadIdx.x != 0) return;
-  LoadState& L = st[l];
-  MinresState& M = ms[l];
+__device__ __forceinline__ void mr_update(const int mode, const int l, const double S, LoadState& L,
+                                          MinresState& M, const HistRef& hist, const unsigned long long hc) {
   if (mode == MR_INIT) {
     M.alpha = M.beta = M.delta1 = M.eps = 0.0;
     M.c = -1.0;
@@ -163,8 +163,18 @@ static __global__ __launch_bounds__(256) void k_mr_scal(const int mode, const do
   M.c = c;
   M.s = s;
   L.res2 = M.phi * M.phi;
-  hist_push(hist, l, L.res2 / L.bb);
+  hist_push(hist, l, L.res2 / L.bb, hc);
   if (L.res2 <= L.tol2 || bn == 0.0) L.active = 0;
+}
+
+static __global__ __launch_bounds__(1024) void k_mr_scal(const int mode, const double* __restrict__ partials,
+                                                        const int pstride, const int nparts,
+                                                        LoadState* __restrict__ st, MinresState* __restrict__ ms,
+                                                        const HistRef hist) {
+  __shared__ double red[16];
+  const int l = blockIdx.x;
+  const double S = mode == MR_INIT ? 0.0 : group_sum(partials, pstride, nparts, l, red);
+  if (threadIdx.x == 0) mr_update(mode, l, S, st[l], ms[l], hist, hist_count(hist, l));
 }
 
 // ----------------------------------------------------------------------------
@@ -199,16 +209,8 @@ static __global__ __launch_bounds__(256) void k_sy_start(const long long F, doub
 // transfers without stopping (the host reports the iteration limit); with
 // gbar_k = 0 there is no CG point and the LQ step is taken; gamma_k = 0 (the
 // system singular on the Krylov space) is a breakdown.
-static __global__ __launch_bounds__(256) void k_sy_scal(const int mode, const double* __restrict__ partials,
-                                                        const int pstride, const int nparts, const int last,
-                                                        LoadState* __restrict__ st, MinresState* __restrict__ ms,
-                                                        const HistRef hist) {
-  __shared__ double red[256];
-  const int l = blockIdx.x;
-  const double S = mode == SY_INIT ? 0.0 : group_sum(partials, pstride, nparts, l, red);
-  if (threadIdx.x != 0) return;
-  LoadState& L = st[l];
-  MinresState& M = ms[l];
+__device__ __forceinline__ void sy_update(const int mode, const int l, const double S, const int last, LoadState& L,
+                                          MinresState& M, const HistRef& hist, const unsigned long long hc) {
   if (mode == SY_INIT) {
     M.alpha = M.beta = M.delta1 = M.eps = 0.0;
     M.c = -1.0;
@@ -238,7 +240,7 @@ static __global__ __launch_bounds__(256) void k_sy_scal(const int mode, const do
     zbar = num / gbar;
     rc = bn * fabs(M.s * M.z1 - M.c * zbar);
   }
-  hist_push(hist, l, rc * rc / L.bb);
+  hist_push(hist, l, rc * rc / L.bb, hc);
   if (gbar != 0.0) {
     L.res2 = rc * rc;
     if (L.res2 <= L.tol2) {
@@ -276,6 +278,16 @@ static __global__ __launch_bounds__(256) void k_sy_scal(const int mode, const do
   M.first = 0.0;
 }
 
+static __global__ __launch_bounds__(1024) void k_sy_scal(const int mode, const double* __restrict__ partials,
+                                                        const int pstride, const int nparts, const int last,
+                                                        LoadState* __restrict__ st, MinresState* __restrict__ ms,
+                                                        const HistRef hist) {
+  __shared__ double red[16];
+  const int l = blockIdx.x;
+  const double S = mode == SY_INIT ? 0.0 : group_sum(partials, pstride, nparts, l, red);
+  if (threadIdx.x == 0) sy_update(mode, l, S, last, st[l], ms[l], hist, hist_count(hist, l));
+}
+
 // SY_STEP: v_{k+1} = vp / beta_{k+1} in place, w_k = c wbar_k + s v_{k+1},
 // wbar_{k+1} = s wbar_k - c v_{k+1}, x += z_k w_k.  SY_TRANSFER: x += zbar_k wbar_k.
 static __global__ __launch_bounds__(256) void k_sy_update(const long long F, double* __restrict__ vp,
@@ -310,46 +322,10 @@ static __global__ __launch_bounds__(256) void k_sy_update(const long long F, dou
   }
 }
 
-// Deterministic final reduction of the partials of group blockIdx.x, then the
-// scalar update of the solver (one workgroup per group).
-// aux (SC_ALPHA): -1 for the unfused CG step (its x pass applies the pending
-// step every iteration); 0 or 1 for the fused step, the buffer this iteration's
-// direction went to (its x pass applies pending steps in pairs).
-static __global__ __launch_bounds__(256) void k_scal(const int mode, const double* __restrict__ partials, const int pstride,
-                                              const int nparts, LoadState* __restrict__ st,
-                                              double* __restrict__ sums, const double tol, const int aux,
-                                              const HistRef hist) {
-  __shared__ double red[256];
-  const int grp = blockIdx.x;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += 256) s += partials[(long long)grp * pstride + i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  const double S = red[0];
-  double S2 = S;
-  if (mode == SC_INITG) {
-    // ||r_0||^2 of a start from initial guesses, group ngroups + grp
-    __syncthreads();
-    double s2 = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += 256) s2 += partials[(long long)(gridDim.x + grp) * pstride + i];
-    red[threadIdx.x] = s2;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-      __syncthreads();
-    }
-    S2 = red[0];
-  }
-  if (threadIdx.x != 0) return;
-  if (mode == SC_SUM) {
-    sums[grp] = S;
-    return;
-  }
-  LoadState& L = st[grp];
+// The scalar update of a load from its sums S, S2 (thread 0).
+__device__ __forceinline__ void scal_update(const int mode, const int grp, const double S, const double S2,
+                                            LoadState& L, const double tol, const int aux, const HistRef& hist,
+                                            const unsigned long long hc) {
   if (mode == SC_INIT || mode == SC_INITG) {
     // SC_INITG: S = ||b||^2 (tolerance), S2 = ||b - L x_0||^2 (start)
     L.bb = S;
@@ -402,12 +378,12 @@ static __global__ __launch_bounds__(256) void k_scal(const int mode, const doubl
     L.beta = S / L.rr;
     L.rr = S;
     L.res2 = S;
-    hist_push(hist, grp, S / L.bb);
+    hist_push(hist, grp, S / L.bb, hc);
     if (S <= L.tol2) L.active = 0;
   } else if (mode == SC_BASIC || mode == SC_OUTER) {
     L.iters += 1;
     L.res2 = S;
-    hist_push(hist, grp, S / L.bb);
+    hist_push(hist, grp, S / L.bb, hc);
     if (!isfinite(S)) {
       L.status = kStatusNumeric;
       L.active = 0;
@@ -415,6 +391,36 @@ static __global__ __launch_bounds__(256) void k_scal(const int mode, const doubl
       L.active = 0;
     }
   }
+}
+
+// Deterministic final reduction of the partials of group blockIdx.x, then the
+// scalar update of the solver (one workgroup per group).
+// aux (SC_ALPHA): -1 for the unfused CG step (its x pass applies the pending
+// step every iteration); 0 or 1 for the fused step, the buffer this iteration's
+// direction went to (its x pass applies pending steps in pairs).
+static __global__ __launch_bounds__(1024) void k_scal(const int mode, const double* __restrict__ partials, const int pstride,
+                                              const int nparts, LoadState* __restrict__ st,
+                                              double* __restrict__ sums, const double tol, const int aux,
+                                              const HistRef hist) {
+  __shared__ double red[16];
+  const int grp = blockIdx.x;
+  // read with the partials, not after them
+  LoadState L;
+  unsigned long long hc = 0;
+  if (mode != SC_SUM) {
+    L = st[grp];
+    hc = hist_count(hist, grp);
+  }
+  const double S = group_sum(partials, pstride, nparts, grp, red);
+  // SC_INITG: ||r_0||^2 of a start from initial guesses, group ngroups + grp
+  const double S2 = mode == SC_INITG ? group_sum(partials, pstride, nparts, gridDim.x + grp, red) : S;
+  if (threadIdx.x != 0) return;
+  if (mode == SC_SUM) {
+    sums[grp] = S;
+    return;
+  }
+  scal_update(mode, grp, S, S2, L, tol, aux, hist, hc);
+  st[grp] = L;
 }
 
 // Deterministic smooth test pattern (kernel-shape timing inputs).

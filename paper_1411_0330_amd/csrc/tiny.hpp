@@ -48,24 +48,11 @@ struct TinyArgs {
   HistRef hist;   // residual history (see hist_push)
 };
 
-// v plus the value that the DPP move brings, zero where it brings none
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWMASK, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWMASK, 0xf, false);
-  return v + __hiloint2double(hi, lo);
-}
-
 // Workgroup sum of one double, returned to every thread (fixed order).  Lanes
 // add by DPP moves: a serial chain of cross-lane LDS permutes was 1 us a sum.
 template <int NT>
 __device__ __forceinline__ double block_allsum(double v, double* red) {
-  v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  v = dpp_add<0x118, 0xf>(v);
-  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-  v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  v = wave_total(v);
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   __syncthreads();
@@ -509,7 +496,7 @@ __global__ __launch_bounds__(NT) void k_tiny_cg(const TinyArgs<T> a) {
     });
     beta = rr_new / rr;
     rr = rr_new;
-    if (tid == 0) hist_push(a.hist, l, rr / st->bb);
+    if (tid == 0) hist_push(a.hist, l, rr / st->bb, hist_count(a.hist, l));
     if (rr <= tol2) {
       done = true;
       break;
