@@ -30,20 +30,20 @@ static int z_inst(hipStream_t s, const Geo& g, const GreenParams& gp, const Gree
 
 #ifdef LSH_Z_FLAT
 // 2D: the y transforms, Gamma and the inverse y transforms in one pass, as the
-// last axis of an nx x 1 x ny grid.  Two components a thread; 64-byte row
-// segments (two tiles of a line on one XCD) rather than whole lines, since a 2D
-// grid has few pencils (512 x 512 FP64 x 2 loads: the three passes took 10.2 +
-// 9.6 + 10.2 us).
+// last axis of an nx x 1 x ny grid.  A 2D grid has few pencils, so the pass is
+// bounded by the chain of one pencil, not by memory: few points a thread (4, or
+// twice the odd factor) and the fewest pencils that fill a wave, at least two.
+// Two loads of a square FP64 grid, with 8 or 12 points and 64-byte row segments
+// and now: 64^2 11.2 and 9.1 us, 128^2 12.9 and 9.9, 192^2 16.0 and 13.2, 256^2
+// 14.0 and 11.0, 512^2 18.1 and 17.2, 1024^2 48.2 and 38.6 (the three separate
+// passes at 512^2: 10.2 + 9.6 + 10.2).  FP32 at 1024 points keeps 8 points and
+// four pencils (26 us; with 4 points 31 to 35).
 template <typename T, int NL>
 static int z2(hipStream_t s, const Geo& g, const GreenParams& gp, const GreenTabs<T>& tb, int zmode, cpx<T>* sm,
               cpx<T>* sn, const cpx<T>* tw, const LoadState* st, int nload, double* qp, int ps) {
-  constexpr int P = odd_part(NL) > 1 ? p_odd<T>(NL, 4) : cmin(8, NL);
-  constexpr int TX = cmax((int)(64 / sizeof(cpx<T>)), cmin(64, 64 * P / NL));
-  // a quarter of the pencils (16-byte segments) where that leaves few workgroups
-  constexpr int TXS = cmin(TX, cmax(TX / 4, cmax(1, 64 * P / NL)));
-  if constexpr (TXS < TX) {
-    if (g.mx / TX < 32) return z_inst<T, NL, 2, TXS, P>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
-  }
+  constexpr bool wide = sizeof(T) == 4 && NL >= 1024;
+  constexpr int P = odd_part(NL) > 1 ? p_odd<T>(NL, 2) : cmin(wide ? 8 : 4, NL);
+  constexpr int TX = cmin(64, cmax(wide ? 4 : 2, 64 * P / NL));
   return z_inst<T, NL, 2, TX, P>(s, g, gp, tb, zmode, sm, sn, tw, st, nload, qp, ps);
 }
 
