@@ -366,7 +366,8 @@ lsh_status lsh_set_variant(lsh_ctx* ctx, int pass, int fp64, int variant);
 lsh_status lsh_get_variants(const lsh_ctx* ctx, int32_t* variants);
 
 /*
- * Autotuner: times every shape of every pass that has several (the others
+ * Autotuner: times every shape of every pass that has several on this grid,
+ * component count and element type (one that falls back to another is left out; the others
  * held at their current choice; the z pass before the y passes, whose layout
  * its shape 5 sets) with HIP events over operator applications
  * of nload loads on the context's own buffers, in the modes the solvers run

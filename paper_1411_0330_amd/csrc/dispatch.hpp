@@ -186,6 +186,34 @@ template <typename T> constexpr bool sv_ok(int n, int tx, int p) {
   return p >= 1 && p <= n && tx >= 1 && tx * (n / p) <= 1024 &&
          (long)(tx + 1) * n * 2 * (int)sizeof(T) + 128 <= kLdsPerWorkgroup;
 }
+// Shapes of the pass with the stored operator, 16 to 192 points along z.  The
+// general rule (256 threads, 8 or 16 points a thread) leaves few workgroups of
+// many registers, which load, compute and store in step, and fills tiles past
+// a short row.  Instead: one 128-byte line of pencils, at least one wave, at most
+// 256 threads (FP64 six components of odd length, 300 VGPRs: 128); up to 64
+// points (odd lengths 96) 4 or 6 a thread; half a line where it divides the row
+// and the line does not (48 and 80 points).  Time before and now, loads = c:
+// scalar FP32 32^3 13.2 and 8.3 us, 64^3 17.2 and 12, 80^3 22.0 and 18.6, 128^3
+// 48.4 and 43.3; scalar FP64 48^3 15.9 and 12.3, 96^3 58.7 and 41, 192^3 322 and
+// 306; elastic FP32 48^3 22.6 and 18.2, 192^3 (2 loads) 331 and 286; FP64 48^3
+// 38.5 and 23.2, 96^3 189 and 164, 192^3 (2 loads) 636 and 575.  The general rule
+// stays for FP64 powers of two with 6 KiB and more a pencil (scalar 128^3 88 us
+// against 92, elastic 64^3 45.0 against 46.5) and from 256 points.
+template <typename T, int C> constexpr bool zs_ok(int n) {
+  return n >= 16 && n < 256 && !(sizeof(T) == 8 && odd_part(n) == 1 && n * C >= 384);
+}
+template <typename T, int C> constexpr int p_zs(int n) {
+  if (odd_part(n) == 1) return C == 3 && n == 128 ? 8 : n <= 32 || C == 3 ? 4 : p_z<T, C>(n);
+  return C == 3 && (n == 48 || (sizeof(T) == 8 && n == 96)) ? p_odd<T>(n, 2) : p_z<T, C>(n);
+}
+template <typename T, int C> constexpr int tx_zs(int n) {
+  const int tpp = n / p_zs<T, C>(n);
+  int tx = cmax(128 / (2 * (int)sizeof(T)), 64 / tpp);
+  const int nt = sizeof(T) == 8 && C == 6 ? 128 : 256;
+  while (tx * tpp > nt) tx /= 2;
+  return tx;
+}
+
 // row-pass points per thread of a variant
 constexpr int rv_p(int mx, int p0, int v) {
   const int p = v == 1 ? p0 / 2 : (v == 2 ? p0 * 2 : (v == 3 ? p0 / 4 : p0));

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -862,14 +863,18 @@ void tune_from_env(lsh_ctx* ctx) {
 // (z variant kZPaired): FP32 six-component fields of a mixed context with the
 // stored operator and 128- or 256-point y and z axes.
 template <typename T>
-bool paired_shape(lsh_ctx* ctx) {
+bool paired_ok(lsh_ctx* ctx) {
   if constexpr (sizeof(T) == 4) {
     const Geo& g = ctx->geo;
     auto ax = [](int n) { return n == 128 || n == 256; };
-    return ctx->precision == LSH_MIXED && !ctx->ovr_sm && ctx->tune[0][PASS_ZG] == kZPaired && g.c == 6 &&
-           ax(g.ny) && ax(g.nz) && Sel<float>::gst(ctx) != nullptr;
+    return ctx->precision == LSH_MIXED && !ctx->ovr_sm && g.c == 6 && ax(g.ny) && ax(g.nz) &&
+           Sel<float>::gst(ctx) != nullptr;
   }
   return false;
+}
+template <typename T>
+bool paired_shape(lsh_ctx* ctx) {
+  return paired_ok<T>(ctx) && ctx->tune[0][PASS_ZG] == kZPaired;
 }
 
 // Where the x passes use the plain layout (the operator passes of
@@ -1689,6 +1694,59 @@ bool pass_has_variants(const lsh_ctx* ctx, int pass) {
     case PASS_ZG: return ctx->c != 2 && (ctx->n[2] == 128 || ctx->n[2] == 256);
     default: return false;
   }
+}
+
+// What variant v of a pass runs on this grid: rows or pencils per workgroup,
+// points per thread, and the kernel (1 the multi-load, 2 the paired z pass).
+// Variants without an instance here fall back, by the launchers' rules, to one
+// that another variant names too; {0, 0, 0} stands for the z pass's 4 and 5
+// where they do.
+using ShapeId = std::array<int, 3>;
+template <typename T, int C>
+ShapeId z_shape(lsh_ctx* ctx, int v) {
+  const int n = ctx->n[2], p0 = p_z<T, C>(n);
+  const bool stored = Sel<T>::gst(ctx) != nullptr;
+  if (v == kZPaired) return paired_ok<T>(ctx) ? ShapeId{8, p0, 2} : ShapeId{};
+  if (v == 4) return sizeof(T) == 4 && ctx->green != LSH_GREEN_FD ? ShapeId{0, p_zm<T, C>(n), 1} : ShapeId{};
+  if (v == 0 && stored && zs_ok<T, C>(n)) {
+    const int p = p_zs<T, C>(n), tx = tx_zs<T, C>(n), mx = ctx->geo.mx;
+    const bool half = sizeof(T) == 4 && tx / 2 * (n / p) >= 64 && mx % tx != 0 && mx % (tx / 2) == 0;
+    return {half ? tx / 2 : tx, p, 0};
+  }
+  const int tx = sv_tx<T>(n, p0, v), p = sv_p(p0, v);
+  return v != 0 && sv_ok<T>(n, tx, p) ? ShapeId{tx, p, 0} : ShapeId{tx_strided<T>(n, p0), p0, 0};
+}
+template <typename T>
+ShapeId pass_shape(lsh_ctx* ctx, int pass, int v) {
+  const int mx = ctx->geo.mx;
+  switch (pass) {
+    case PASS_XFWD: {
+      const int p = v == 0 ? p_xfwd<T>(mx) : rv_p(mx, p_xfwd<T>(mx), v);
+      return {256 / (mx / p), p, 0};
+    }
+    case PASS_XINV: {
+      const int p0 = ctx->c == 6 ? p_xinv<T, 6>(mx) : p_xinv<T, 3>(mx);   // two components as three
+      const int p = v == 0 ? p0 : rv_p(mx, p0, v);
+      return {256 / (mx / p), p, 0};
+    }
+    case PASS_Y: {
+      const int n = ctx->n[1], p0 = p_y<T>(n), tx = sv_tx<T>(n, p0, v), p = sv_p(p0, v);
+      return v != 0 && sv_ok<T>(n, tx, p) ? ShapeId{tx, p, 0} : ShapeId{tx_strided<T>(n, p0), p0, 0};
+    }
+    default: return ctx->c == 6 ? z_shape<T, 6>(ctx, v) : z_shape<T, 3>(ctx, v);
+  }
+}
+// The variants of a pass that differ here, the lowest number of each shape.
+std::vector<int> distinct_variants(lsh_ctx* ctx, int pass, bool fp64) {
+  std::vector<int> vs;
+  std::vector<ShapeId> seen{ShapeId{}};
+  for (int v = 0; v < pass_variants(pass); ++v) {
+    const ShapeId id = fp64 ? pass_shape<double>(ctx, pass, v) : pass_shape<float>(ctx, pass, v);
+    if (std::find(seen.begin(), seen.end(), id) != seen.end()) continue;
+    seen.push_back(id);
+    vs.push_back(v);
+  }
+  return vs;
 }
 
 int pass_class(int pass, bool fp64) {
@@ -2734,7 +2792,7 @@ lsh_status lsh_autotune(lsh_ctx* ctx, int nload, const char* cache_path, int32_t
       const int cls = pass_class(pass, fp64);
       double best_t = 1e300;
       int best_v = ctx->tune[prec][pass];
-      for (int v = 0; v < pass_variants(pass); ++v) {
+      for (int v : distinct_variants(ctx, pass, fp64)) {
         ctx->tune[prec][pass] = v;
         // one warm-up application, then the timed ones
         STCHK(timing_iteration(ctx, nload, fp64));

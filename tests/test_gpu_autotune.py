@@ -1,0 +1,31 @@
+"""What the autotuner may choose: shapes that exist on the grid at hand."""
+import numpy as np
+import pytest
+
+from paper_1411_0330_amd import inputs as I
+
+from .gpu_util import context
+
+pytestmark = pytest.mark.gpu
+
+ELAS = np.stack([I.elastic_from_young(1.0, 0.3), I.elastic_from_young(10.0, 0.2)])
+C0 = I.elastic_from_young(0.5, 0.3)
+SCAL = np.stack([I.scalar_isotropic(a, 3) for a in (1.0, 10.0)])
+S0 = I.scalar_isotropic(0.5, 3)
+
+
+def _ctx(lsh, physics, shape, precision, nload, green="filtered"):
+    moduli, ref = (ELAS, C0) if physics == "elastic" else (SCAL, S0)
+    return context(lsh, I.random_phases(shape, 2, seed=3), moduli, ref, physics, green, precision, nload)
+
+
+@pytest.mark.parametrize("physics,precision", [("scalar", "mixed"), ("scalar", "fp64"), ("elastic", "fp64")])
+def test_tuner_chooses_no_shape_without_an_instance(lsh, physics, precision):
+    # z shapes 4 (FP32) and 5 (FP32, six components, 128- or 256-point y axes)
+    # fall back to shape 0 elsewhere; on this grid, a few microseconds a pass,
+    # such a duplicate would come out ahead in about every other search
+    ctx = _ctx(lsh, physics, (128, 8, 16), precision, 2)
+    for _ in range(8):
+        v, _ = ctx.autotune(2)
+        assert v["fp32"][2] <= 4 and v["fp64"][2] <= 3
+        assert all(x <= 3 for x in v["fp32"][:2] + v["fp32"][3:] + v["fp64"])
