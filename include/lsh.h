@@ -369,7 +369,8 @@ lsh_status lsh_get_variants(const lsh_ctx* ctx, int32_t* variants);
  * Autotuner: times every shape of every pass that has several on this grid,
  * component count and element type (one that falls back to another is left out; the others
  * held at their current choice; the z pass before the y passes, whose layout
- * its shape 5 sets) with HIP events over operator applications
+ * its shape 5 sets; where that shape stands against plane passes, which it
+ * cannot use, the z shapes are ranked by the time of all passes) with HIP events over operator applications
  * of nload loads on the context's own buffers, in the modes the solvers run
  * (the CG modes for FP32 fields of a mixed context and FP64 fields of an FP64
  * context, the refinement modes for the FP64 passes of a mixed context), and

@@ -2789,20 +2789,29 @@ lsh_status lsh_autotune(lsh_ctx* ctx, int nload, const char* cache_path, int32_t
       if (pg && !paired && pass != PASS_ZG && (pass != PASS_Y || with_y(ctx, pg))) continue;
       // the fused CG x pass has one shape (CG fields: FP32 of a mixed context, FP64 of an FP64 one)
       if (pass == PASS_XFWD && ctx->cg_fused && (!fp64 || ctx->precision != LSH_MIXED)) continue;
-      const int cls = pass_class(pass, fp64);
+      // z shape 5 takes the plane passes away (four passes along x and y instead
+      // of two; elastic 128^3 x 6 FP32: z 178 us against 196, the whole step 942
+      // against 776), so there the z shapes are ranked by all passes of a step
+      std::vector<int> cls{pass_class(pass, fp64)};
+      if (pass == PASS_ZG && pg && !fp64 && paired_ok<float>(ctx))
+        for (int p : {PASS_XFWD, PASS_Y, PASS_XINV}) cls.push_back(pass_class(p, fp64));
+      auto spent = [&] {
+        drain_timers(ctx);
+        double t = 0.0;
+        for (int k : cls) t += ctx->tsum[k];
+        return t;
+      };
       double best_t = 1e300;
       int best_v = ctx->tune[prec][pass];
       for (int v : distinct_variants(ctx, pass, fp64)) {
         ctx->tune[prec][pass] = v;
         // one warm-up application, then the timed ones
         STCHK(timing_iteration(ctx, nload, fp64));
-        drain_timers(ctx);
-        const double t0 = ctx->tsum[cls];
-        const long long c0 = ctx->tcount[cls];
+        const double t0 = spent();
+        const long long c0 = ctx->tcount[cls[0]];
         for (int r = 0; r < reps; ++r) STCHK(timing_iteration(ctx, nload, fp64));
-        drain_timers(ctx);
-        const long long dc = ctx->tcount[cls] - c0;
-        const double t = dc > 0 ? (ctx->tsum[cls] - t0) / (double)dc : 1e300;
+        const double t1 = spent();
+        const double t = ctx->tcount[cls[0]] > c0 ? t1 - t0 : 1e300;
         if (t < best_t) {
           best_t = t;
           best_v = v;
