@@ -377,7 +377,9 @@ lsh_status lsh_get_variants(const lsh_ctx* ctx, int32_t* variants);
  * keeps the fastest.
  * With cache_path (may be NULL) the choice is looked up first in, and
  * afterwards written to, a text file with one line per key: device, grid,
- * components, precision, nload, Green operator and material form.  A cache
+ * components, precision, nload, Green operator and material form, whether
+ * plane passes or row blocks run (LSH_PLANE), and the tile of z shape 0 where
+ * it has its own.  A cache
  * hit runs nothing on the GPU (*from_cache = 1).  Needs a prepared context
  * (reference and material set); invalidates the last solution.  variants
  * (may be NULL) receives the 8 choices as lsh_get_variants.

@@ -1788,12 +1788,28 @@ lsh_status timing_iteration(lsh_ctx* ctx, int nload, bool fp64) {
   return inverse_x<double>(ctx, 0, nload, XI_CG, ctx->ptr<double>(ctx->off.p64), q, nullptr, st, parts, nullptr);
 }
 
-std::string tune_key(const lsh_ctx* ctx, int nload) {
+// Whether any x pass runs as a plane pass or over row blocks.
+template <typename T>
+bool xy_blocks(lsh_ctx* ctx) { return plane_of<T>(ctx, true) != nullptr || plane_of<T>(ctx, false) != nullptr; }
+
+// What a choice of shapes was timed against: the grid and the problem, whether
+// plane passes or row blocks take x and y (LSH_PLANE), and the z pass's shape 0
+// where it has a tile of its own.
+std::string tune_key(lsh_ctx* ctx, int nload) {
   std::ostringstream k;
-  k << "gfx950 " << ctx->n[0] << "x" << ctx->n[1] << "x" << ctx->n[2] << " c" << ctx->c
-    << (ctx->precision == LSH_MIXED ? " mixed" : " fp64") << " L" << nload << " green" << ctx->green
-    << (ctx->mat_voxel ? " voxel" : (ctx->iso ? " iso" : " full"))
-    << ((Sel<float>::gst(const_cast<lsh_ctx*>(ctx)) || Sel<double>::gst(const_cast<lsh_ctx*>(ctx))) ? " stored" : "");
+  const bool mixed = ctx->precision == LSH_MIXED;
+  k << "gfx950 " << ctx->n[0] << "x" << ctx->n[1] << "x" << ctx->n[2] << " c" << ctx->c << (mixed ? " mixed" : " fp64")
+    << " L" << nload << " green" << ctx->green << (ctx->mat_voxel ? " voxel" : (ctx->iso ? " iso" : " full"))
+    << ((Sel<float>::gst(ctx) || Sel<double>::gst(ctx)) ? " stored" : "");
+  if ((mixed && xy_blocks<float>(ctx)) || xy_blocks<double>(ctx)) k << " blocks";
+  if (pass_has_variants(ctx, PASS_ZG)) {
+    const int n = ctx->n[2];
+    const ShapeId z = mixed ? pass_shape<float>(ctx, PASS_ZG, 0) : pass_shape<double>(ctx, PASS_ZG, 0);
+    const int p = mixed ? (ctx->c == 6 ? p_z<float, 6>(n) : p_z<float, 3>(n))
+                        : (ctx->c == 6 ? p_z<double, 6>(n) : p_z<double, 3>(n));
+    const int tx = mixed ? tx_strided<float>(n, p) : tx_strided<double>(n, p);
+    if (z[0] != tx || z[1] != p) k << " z" << z[0] << "x" << z[1];
+  }
   return k.str();
 }
 

@@ -51,3 +51,23 @@ def test_tuner_weighs_z_shape_5_against_the_plane_passes(lsh):
     v, _ = ctx.autotune(nload)
     assert v["fp32"][2] != 5
     assert step_ms(v["fp32"][2]) <= 1.05 * plane
+
+
+@pytest.mark.parametrize("physics,shape", [("scalar", (128, 16, 16)), ("elastic", (128, 16, 16)),
+                                           ("scalar", (32, 128, 128)), ("scalar", (4, 256, 192))])
+def test_tuner_cache_tells_the_passes_apart(lsh, monkeypatch, tmp_path, physics, shape):
+    # a choice timed against the separate passes is no choice for a grid that
+    # runs plane passes or row blocks, and the other way round; nor is a line
+    # of before these passes and the z tiles of shape 0, whose key names neither
+    cache = tmp_path / "tune.txt"
+    z, y, x = shape
+    c = 6 if physics == "elastic" else 3
+    cache.write_text(f"gfx950 {x}x{y}x{z} c{c} mixed L1 green1 iso stored = 0 3 3 1 1 3 3 1\n")
+    for on in ("1", "0"):
+        monkeypatch.setenv("LSH_PLANE", on)
+        v, hit = _ctx(lsh, physics, shape, "mixed", 1).autotune(1, cache)
+        old = z != 128 and on == "0"   # nothing new runs there
+        assert hit == old
+        v2, hit = _ctx(lsh, physics, shape, "mixed", 1).autotune(1, cache)
+        assert hit and v2 == v
+    assert len(cache.read_text().splitlines()) == (3 if z == 128 else 2)
