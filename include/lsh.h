@@ -373,8 +373,9 @@ lsh_status lsh_get_variants(const lsh_ctx* ctx, int32_t* variants);
  * cannot use, the z shapes are ranked by the time of all passes) with HIP events over operator applications
  * of nload loads on the context's own buffers, in the modes the solvers run
  * (the CG modes for FP32 fields of a mixed context and FP64 fields of an FP64
- * context, the refinement modes for the FP64 passes of a mixed context), and
- * keeps the fastest.
+ * context, the refinement modes for the FP64 passes of a mixed context; a pass
+ * that these run as plane pass or row block, in an application L tau or, FP64,
+ * a fixed-point step), and keeps the fastest.
  * With cache_path (may be NULL) the choice is looked up first in, and
  * afterwards written to, a text file with one line per key: device, grid,
  * components, precision, nload, Green operator and material form, whether

@@ -1690,7 +1690,7 @@ bool pass_has_variants(const lsh_ctx* ctx, int pass) {
   switch (pass) {
     case PASS_XFWD:
     case PASS_XINV: return ctx->geo.mx == 64 || ctx->geo.mx == 128;
-    case PASS_Y: return ctx->n[1] == 128 || ctx->n[1] == 256;
+    case PASS_Y: return ctx->dim == 3 && (ctx->n[1] == 128 || ctx->n[1] == 256);   // 2D: in the Green pass
     case PASS_ZG: return ctx->c != 2 && (ctx->n[2] == 128 || ctx->n[2] == 256);
     default: return false;
   }
@@ -1754,13 +1754,46 @@ int pass_class(int pass, bool fp64) {
   return base + (fp64 ? 1 : 0);
 }
 
+// The application that runs the variants of a pass: the step of the solve (CG,
+// or the refinement of a mixed context) where its passes are the ones in
+// registers; else the application L tau (row blocks may take the CG passes
+// alone); else, in FP64, the fixed-point schemes, whose inverse passes are
+// always separate.  None for the fused CG x pass, which has one shape.
+enum : int { TM_NONE = -1, TM_STEP = 0, TM_APPLY = 1, TM_FIXED = 2 };
+template <typename T>
+int timing_mode(lsh_ctx* ctx, int pass) {
+  const bool refine = sizeof(T) == 8 && ctx->precision == LSH_MIXED;
+  const bool fused = ctx->cg_fused && !refine;
+  if (pass == PASS_ZG) return TM_STEP;
+  if (pass == PASS_XFWD) return fused || (refine && plane_of<T>(ctx, false)) ? TM_NONE : TM_STEP;
+  const PlaneGeo* pg = nullptr;
+  if (refine) pg = plane_inv<T>(ctx, XI_IRRES, nullptr, nullptr);
+  else if (fused && !paired_shape<T>(ctx)) pg = plane_inv<T>(ctx, XI_CGR, nullptr, nullptr);
+  if (!pg || (pass == PASS_Y && !with_y(ctx, pg))) return TM_STEP;
+  if (pass == PASS_XINV && !plane_inv<T>(ctx, XI_CG, nullptr, nullptr)) return TM_APPLY;
+  return sizeof(T) == 8 ? TM_FIXED : TM_NONE;
+}
+
 // One operator application in the modes the solvers run, on the workspace's
 // own fields (timing input): the CG modes (x += alpha p and p = r + beta p
 // fused into the x pass, q and p.q out of the last) for FP32 fields of a mixed
 // context and FP64 fields of an FP64 context, the refinement modes (x64 += d,
 // FP64 residual to FP32) for the FP64 passes of a mixed context.
-lsh_status timing_iteration(lsh_ctx* ctx, int nload, bool fp64) {
+// TM_APPLY and TM_FIXED are the application q = L tau and the fixed-point step.
+lsh_status timing_iteration(lsh_ctx* ctx, int nload, bool fp64, int how) {
   double* parts = ctx->ptr<double>(ctx->off.partials);
+  if (how != TM_STEP) {
+    if (!fp64) {
+      float* q = reinterpret_cast<float*>(Sel<float>::sm(ctx));
+      const float* v = ctx->ptr<float>(ctx->off.p32);
+      return operator_pass<float>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, ctx->ptr<LoadState>(ctx->off.st_in),
+                                  XI_CG, v, q, nullptr, parts, nullptr);
+    }
+    double* q = reinterpret_cast<double*>(Sel<double>::sm(ctx));
+    const double* v = ctx->ptr<double>(ctx->off.x64);
+    return operator_pass<double>(ctx, 0, nload, XF_PLAIN, v, nullptr, nullptr, ctx->ptr<LoadState>(ctx->off.st_out),
+                                 how == TM_FIXED ? XI_BASIC : XI_CG, v, q, nullptr, parts, nullptr);
+  }
   if (!fp64 && ctx->cg_fused)
     return cg_fused_step<float>(ctx, 0, nload, ctx->ptr<float>(ctx->off.d32), ctx->ptr<float>(ctx->off.r32),
                                 ctx->ptr<float>(ctx->off.p32b), ctx->ptr<float>(ctx->off.p32), 0,
@@ -2797,19 +2830,13 @@ lsh_status lsh_autotune(lsh_ctx* ctx, int nload, const char* cache_path, int32_t
     for (int pi = 0; pi < NPASS; ++pi) {
       const int pass = order[pi];
       if (!pass_has_variants(ctx, pass)) continue;
-      // x and y run as plane passes, which have one shape
-      const bool paired = !fp64 && paired_shape<float>(ctx);
-      const int mode = fp64 && ctx->precision == LSH_MIXED ? XI_IRRES : XI_CGR;
-      const PlaneGeo* pg = fp64 ? plane_inv<double>(ctx, mode, nullptr, nullptr)
-                                : plane_inv<float>(ctx, mode, nullptr, nullptr);
-      if (pg && !paired && pass != PASS_ZG && (pass != PASS_Y || with_y(ctx, pg))) continue;
-      // the fused CG x pass has one shape (CG fields: FP32 of a mixed context, FP64 of an FP64 one)
-      if (pass == PASS_XFWD && ctx->cg_fused && (!fp64 || ctx->precision != LSH_MIXED)) continue;
+      const int how = fp64 ? timing_mode<double>(ctx, pass) : timing_mode<float>(ctx, pass);
+      if (how == TM_NONE) continue;
       // z shape 5 takes the plane passes away (four passes along x and y instead
       // of two; elastic 128^3 x 6 FP32: z 178 us against 196, the whole step 942
       // against 776), so there the z shapes are ranked by all passes of a step
       std::vector<int> cls{pass_class(pass, fp64)};
-      if (pass == PASS_ZG && pg && !fp64 && paired_ok<float>(ctx))
+      if (pass == PASS_ZG && !fp64 && paired_ok<float>(ctx) && plane_of<float>(ctx, true))
         for (int p : {PASS_XFWD, PASS_Y, PASS_XINV}) cls.push_back(pass_class(p, fp64));
       auto spent = [&] {
         drain_timers(ctx);
@@ -2822,10 +2849,10 @@ lsh_status lsh_autotune(lsh_ctx* ctx, int nload, const char* cache_path, int32_t
       for (int v : distinct_variants(ctx, pass, fp64)) {
         ctx->tune[prec][pass] = v;
         // one warm-up application, then the timed ones
-        STCHK(timing_iteration(ctx, nload, fp64));
+        STCHK(timing_iteration(ctx, nload, fp64, how));
         const double t0 = spent();
         const long long c0 = ctx->tcount[cls[0]];
-        for (int r = 0; r < reps; ++r) STCHK(timing_iteration(ctx, nload, fp64));
+        for (int r = 0; r < reps; ++r) STCHK(timing_iteration(ctx, nload, fp64, how));
         const double t1 = spent();
         const double t = ctx->tcount[cls[0]] > c0 ? t1 - t0 : 1e300;
         if (t < best_t) {

@@ -71,3 +71,36 @@ def test_tuner_cache_tells_the_passes_apart(lsh, monkeypatch, tmp_path, physics,
         v2, hit = _ctx(lsh, physics, shape, "mixed", 1).autotune(1, cache)
         assert hit and v2 == v
     assert len(cache.read_text().splitlines()) == (3 if z == 128 else 2)
+
+
+@pytest.mark.parametrize("physics,shape,precision,pass_,cls", [
+    ("scalar", (64, 128, 128), "fp64", 3, "xinv_f64"), ("elastic", (32, 256, 256), "mixed", 3, "xinv_f32")])
+def test_tuner_times_the_passes_that_planes_leave(lsh, physics, shape, precision, pass_, cls):
+    # plane passes take the CG step, but not the inverse passes of the
+    # fixed-point schemes; row blocks take CG's x passes at 256 points, but not
+    # those of an application: the tuner has to find a shape for them
+    ctx = _ctx(lsh, physics, shape, precision, 2)
+    fp64 = precision == "fp64"
+    import torch
+    tau = torch.randn((2, ctx.c) + shape, device="cuda", dtype=torch.float64 if fp64 else torch.float32)
+
+    def ms(v):
+        ctx.set_variant(pass_, fp64, v)
+        ctx.set_timing(True)
+        if fp64:
+            ctx.solve(np.eye(ctx.c)[:2], "basic", tol=1e-12, maxit=8)
+        else:
+            for _ in range(8):
+                ctx.apply(tau)
+        t = ctx.kernel_times()[cls]
+        ctx.set_timing(False)
+        return t[0] / t[1]
+
+    [ms(v) for v in range(4)]   # first launches
+    t = [ms(v) for v in range(4)]
+    worst = int(np.argmax(t))
+    assert t[worst] > 1.15 * min(t), t
+    ctx.set_variant(pass_, fp64, worst)
+    v, _ = ctx.autotune(2)
+    chosen = v["fp64" if fp64 else "fp32"][pass_]
+    assert ms(chosen) <= 1.1 * min(t), (t, v)
