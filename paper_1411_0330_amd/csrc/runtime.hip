@@ -246,6 +246,7 @@ struct lsh_ctx {
   } graphs[5];   // CG FP64, CG FP32, fixed point; CG FP64 and FP32 of odd iterations (fused step)
   long long graph_epoch = 0;  // bumped whenever captured kernel arguments may change
   unsigned long long* prog = nullptr;   // progress words of the running iteration loop (see progress_push)
+  unsigned sched = 0;                   // how that loop waits (the device's scheduling flags)
   std::string graph_args;     // the material's kernel arguments at the last bump (values, see build_tables)
 
   // timing
@@ -1337,6 +1338,8 @@ lsh_status read_states(lsh_ctx* ctx, size_t off, int nload, std::vector<LoadStat
 struct Progress {
   lsh_ctx* ctx;
   explicit Progress(lsh_ctx* c, const std::vector<LoadState>& h) : ctx(c) {
+    unsigned flags = 0;
+    ctx->sched = hipGetDeviceFlags(&flags) == hipSuccess ? flags & hipDeviceScheduleMask : 0;
     unsigned long long* w = progress_words(ctx);
     ctx->nact = 0;
     for (size_t l = 0; l < h.size(); ++l) {
@@ -1354,9 +1357,16 @@ struct Progress {
 // running loop or has stopped; *any tells whether one still iterates.  The
 // stream bounds the wait: after 50 ms without an answer it is asked for errors
 // and completion (not sooner: a query can queue a marker behind the iteration).
+// Outside a fiber the core is given up as the device's scheduling flags ask:
+// with hipDeviceScheduleYield between two looks, with
+// hipDeviceScheduleBlockingSync by sleeping, from 200 us on (the sleep ends up
+// to 0.1 ms late, which one queued iteration of that length covers; 30 MINRES
+// steps of 128^3 x 6 elastic FP64 loads take 81 ms, of CPU time 77 ms without it).
 lsh_status progress_wait(lsh_ctx* ctx, const std::vector<LoadState>& h, int done, bool* any) {
   const unsigned long long* w = progress_words(ctx);
   auto asked = std::chrono::steady_clock::now();
+  const auto begun = asked;
+  bool asleep = false;
   for (unsigned spin = 1;; ++spin) {
     bool ready = true;
     int act = 0;
@@ -1370,7 +1380,7 @@ lsh_status progress_wait(lsh_ctx* ctx, const std::vector<LoadState>& h, int done
     *any = act > 0;
     ctx->nact = act;
     if (ready) return LSH_OK;
-    if (spin % 1024 == 0 && std::chrono::steady_clock::now() - asked > std::chrono::milliseconds(50)) {
+    if ((asleep || spin % 1024 == 0) && std::chrono::steady_clock::now() - asked > std::chrono::milliseconds(50)) {
       asked = std::chrono::steady_clock::now();
       const hipError_t q = hipStreamQuery(ctx->stream);
       if (q == hipSuccess) {
@@ -1391,6 +1401,13 @@ lsh_status progress_wait(lsh_ctx* ctx, const std::vector<LoadState>& h, int done
         int cur = -1;
         if (hipGetDevice(&cur) == hipSuccess && cur != ctx->ws_device) HIPCHK(hipSetDevice(ctx->ws_device));
       }
+    } else if (ctx->sched == hipDeviceScheduleBlockingSync) {
+      if (!asleep && spin % 64 == 0)
+        asleep = std::chrono::steady_clock::now() - begun > std::chrono::microseconds(200);
+      if (asleep) std::this_thread::sleep_for(std::chrono::microseconds(50));
+      else _mm_pause();
+    } else if (ctx->sched == hipDeviceScheduleYield) {
+      std::this_thread::yield();
     } else {
       _mm_pause();
     }
