@@ -963,11 +963,10 @@ const PlaneGeo* plane_of(lsh_ctx* ctx, bool cg) {
 }
 // whether pg is a geometry of planes (their y transform included), not of row blocks
 bool with_y(const lsh_ctx* ctx, const PlaneGeo* pg) { return pg == &ctx->pgeo[0] || pg == &ctx->pgeo[1]; }
-// Forward in mode xmode: the CG mode needs the local term in its short form.
+// Forward of a plain field or a refinement (the CG step takes its geometry from plane_inv).
 template <typename T>
-const PlaneGeo* plane_fwd(lsh_ctx* ctx, int xmode, const void* src) {
-  if (xmode == XF_CG && !ctx->iso) return nullptr;
-  return aligned16(src) ? plane_of<T>(ctx, xmode == XF_CG) : nullptr;
+const PlaneGeo* plane_fwd(lsh_ctx* ctx, const void* src) {
+  return aligned16(src) ? plane_of<T>(ctx, false) : nullptr;
 }
 // Inverse in mode `mode` with field tau and output out: the fixed-point modes
 // couple the components of Gamma tau and keep the separate passes, as do
@@ -1017,7 +1016,8 @@ lsh_status forward_part(lsh_ctx* ctx, int l0, int nload, int xmode, const T* src
   const double xin = xmode == XF_CG ? (ctx->xf_first ? 3.0 : 5.0) * cvs
                                     : (xmode == XF_IRX ? 2.0 * cvs + 4.0 * ctx->F : cvs);
   cpx<T>* sp = gamma ? paired_spectrum<T>(ctx, l0) : nullptr;
-  const PlaneGeo* pg = (sp || xmode == XF_CG) ? nullptr : plane_fwd<T>(ctx, xmode, src);
+  // (the unfused CG x pass has no plane instance)
+  const PlaneGeo* pg = (sp || xmode == XF_CG) ? nullptr : plane_fwd<T>(ctx, src);
   if (pg) {
     Scope sc(ctx, kcls<T>(K_XFWD), nl * (xin + spec));
     PlaneFwdArgs<T> pa = plane_fwd_args<T>(ctx, *pg, sm, sn, st);
