@@ -353,11 +353,20 @@ lsh_status lsh_spectrum_bytes(const lsh_ctx* ctx, int dtype, size_t* bytes);
  * filtered operator, 128- or 256-point y and z axes; otherwise shape 0 runs;
  * the copy lives in the FP64 spectrum buffer of the workspace, so the
  * workspace size does not change).  Every shape computes the
- * same result up to rounding; only speed differs.  Grids whose x-y planes fit
- * one workgroup (squares up to 160 x 160 in FP32 and 128 x 128 in FP64, and
- * other small planes; three dimensions, isotropic phases or per-voxel moduli)
- * run x and y as one pass of one shape whatever these choices say (z shape 5
- * excepted); LSH_PLANE=0 in the environment keeps the separate passes.
+ * same result up to rounding; only speed differs.  Some passes have one shape
+ * whatever these choices say (tensors on 16 bytes; the inverse with isotropic
+ * phases or per-voxel moduli, and not in the fixed-point schemes):
+ *  - x and y run as one pass on 3D grids whose x-y planes fit one workgroup:
+ *    squares of 16 to 160 (FP64 128) points of the compiled lengths and any other plane of
+ *    48 KiB (FP64 32 KiB); above 32 KiB only with 48 planes times components
+ *    or more (not with z shape 5);
+ *  - x runs over blocks of rows on other grids with rows of 48, 80, 96, 160 or
+ *    192 points, and with 64- to 1024-point rows (powers of two) of smaller
+ *    fields: CG on fields below 64 MB (FP64 scalar; FP32 elastic, or scalar from 128
+ *    points), other applications on scalar FP64 fields below 64 MB (2D: 16 MB);
+ *  - 2D grids transform y in the z pass, which has one shape for them.
+ * LSH_PLANE=0 in the environment keeps x and y as separate passes with their
+ * choices (in 3D).
  * lsh_get_variants writes the 8 current
  * choices (FP32 passes, then FP64).  The environment variable LSH_TUNE (for
  * example "zg32=1,xinv64=2") sets them when the context is created.

@@ -344,9 +344,10 @@ void drain_timers(lsh_ctx* ctx) {
 
 // ------------------------- waits and the ensemble fibers ----------------
 // lsh_solve_many runs the solves of an ensemble as fibers (user-level
-// contexts) on the calling thread.  Every wait for the GPU inside a solve
-// (wait_stream) records an event on the context's stream and, inside a
-// fiber, hands the thread to the next fiber until the event has passed; so
+// contexts) on the calling thread.  A wait for the GPU inside a solve hands
+// the thread to the next fiber: wait_stream until an event that it records on
+// the context's stream has passed, progress_wait until the loads' progress
+// words have come; so
 // the members' kernels overlap on their own streams while every HIP call
 // comes from one host thread, one member at a time.
 struct Fiber {
@@ -477,7 +478,8 @@ void compute_layout(lsh_ctx* ctx) {
   ctx->h_guess.assign(L, 0);
   // partial sums: the largest grid of any reducing kernel, per group
   // (the fused CG step writes the x pass's and the z pass's partials side by side)
-  // (the fused CG step's x pass: rows, or one partial per component and plane or row block)
+  // (the fused CG step's x pass: rows, or one partial per component and plane or row block; no
+  // more than run, since a larger stride moves the fields behind and cost the z pass 2 %)
   long long xmax = std::max(xinv_blocks(ctx->geo, 2), (long long)ctx->geo.nz * c);
   xmax = std::max(xmax, std::max(row_blocks<float>(ctx->geo), row_blocks<double>(ctx->geo)));
   long long pmax = xmax + zg_blocks_max<float>(ctx->geo);
@@ -1456,7 +1458,8 @@ lsh_status run_iteration(lsh_ctx* ctx, int slot, long long key, F&& enqueue) {
 // CG iterations on (x, r, p) with q held in the spectrum buffer; returns after
 // convergence of every load, or maxit iterations.  The fused step alternates
 // its directions between p (even iterations) and pb (odd ones), one captured
-// graph per parity; the unfused step and the persistent loop use p alone.
+// graph per parity; the unfused step uses p alone, and the persistent loop
+// keeps its directions on chip.
 template <typename T>
 lsh_status cg_loop(lsh_ctx* ctx, int nload, T* x, T* r, T* p, T* pb, LoadState* st, size_t st_off, int maxit,
                    std::vector<LoadState>& hst, bool flush = true) {

@@ -9,8 +9,9 @@
 // (and z) transforms in place in LDS (plane.hpp: decimation in frequency, then
 // in time, one butterfly per thread and step, lanes along rows or columns),
 // the Green operator with p.Gamma p (Parseval), the way back, r -= alpha Lp
-// with ||r||^2.  It is bounded by LDS traffic and the latency of its 12 (2D) to
-// 16 (3D) barrier-separated sweeps over the spectrum; the loop that it replaced
+// with ||r||^2.  It is bounded by LDS traffic and the latency of its
+// barrier-separated sweeps over the spectrum, by the stages of the axes 9 (8^2)
+// to 13 (32^2 and 64^2) in 2D, 11 (8^3) and 15 (16^3); the loop that it replaced
 // passed through memory between them.  One iteration of two loads, before and
 // now: FP64 64^2 34 and 15.5 us, 32^2 22 and 8.3, 8^2 18 and 5.5, scalar 8^3 24
 // and 7.6, scalar 16^3 81 and 34 (40 with one kernel per pass), elastic 8^3 51
