@@ -192,11 +192,12 @@ template <typename T> constexpr bool sv_ok(int n, int tx, int p) {
 // a short row.  Instead: one 128-byte line of pencils, at least one wave, at most
 // 256 threads (FP64 six components of odd length, 300 VGPRs: 128); up to 64
 // points (odd lengths 96) 4 or 6 a thread; half a line where it divides the row
-// and the line does not (48 and 80 points).  Time before and now, loads = c:
-// scalar FP32 32^3 13.2 and 8.3 us, 64^3 17.2 and 12, 80^3 22.0 and 18.6, 128^3
-// 48.4 and 43.3; scalar FP64 48^3 15.9 and 12.3, 96^3 58.7 and 41, 192^3 322 and
-// 306; elastic FP32 48^3 22.6 and 18.2, 192^3 (2 loads) 331 and 286; FP64 48^3
-// 38.5 and 23.2, 96^3 189 and 164, 192^3 (2 loads) 636 and 575.  The general rule
+// and the line does not (48 and 80 points).  Time in a CG step with separate x
+// and y passes, general rule and this, loads = c unless stated: scalar FP32 32^3
+// 11.3 and 6.0 us, 64^3 15.8 and 10.8, 80^3 20.9 and 18.6, 128^3 45.6 and 40.4;
+// scalar FP64 48^3 14.9 and 11.5, 96^3 63.8 and 44.6, 192^3 314 and 306; elastic
+// FP32 48^3 22.8 and 19.6, 192^3 (2 loads) 333 and 296; FP64 48^3 44.6 and 23.8,
+// 96^3 199 and 173, 192^3 (2 loads) 649 and 601.  The general rule
 // stays for FP64 powers of two with 6 KiB and more a pencil (scalar 128^3 88 us
 // against 92, elastic 64^3 45.0 against 46.5) and from 256 points.
 template <typename T, int C> constexpr bool zs_ok(int n) {
