@@ -1359,12 +1359,23 @@ struct Progress {
 // running loop or has stopped; *any tells whether one still iterates.  The
 // stream bounds the wait: after 50 ms without an answer it is asked for errors
 // and completion (not sooner: a query can queue a marker behind the iteration).
+// With kernel timing on the states (at st_off) are read back instead, after
+// every iteration: the bytes of the timed launches are those of the loads that
+// iterate in them, and no empty iteration is among them.
 // Outside a fiber the core is given up as the device's scheduling flags ask:
 // with hipDeviceScheduleYield between two looks, with
 // hipDeviceScheduleBlockingSync by sleeping, from 200 us on (the sleep ends up
 // to 0.1 ms late, which one queued iteration of that length covers; 30 MINRES
 // steps of 128^3 x 6 elastic FP64 loads take 81 ms, of CPU time 77 ms without it).
-lsh_status progress_wait(lsh_ctx* ctx, const std::vector<LoadState>& h, int done, bool* any) {
+lsh_status progress_wait(lsh_ctx* ctx, const std::vector<LoadState>& h, size_t st_off, int done, bool* any) {
+  if (ctx->timing) {
+    std::vector<LoadState> now;
+    STCHK(read_states(ctx, st_off, (int)h.size(), now));
+    ctx->nact = 0;
+    for (const LoadState& s : now) ctx->nact += s.active != 0;
+    *any = ctx->nact > 0;
+    return LSH_OK;
+  }
   const unsigned long long* w = progress_words(ctx);
   auto asked = std::chrono::steady_clock::now();
   const auto begun = asked;
@@ -1506,7 +1517,7 @@ lsh_status cg_loop(lsh_ctx* ctx, int nload, T* x, T* r, T* p, T* pb, LoadState* 
     ctx->xf_first = it == 0;
     par = ctx->cg_fused ? (it & 1) : 0;
     STCHK(run_iteration(ctx, (sizeof(T) == 8 ? 0 : 1) + 3 * par, key, iteration));
-    STCHK(progress_wait(ctx, hst, it, &any));
+    STCHK(progress_wait(ctx, hst, st_off, it, &any));
     if (!any) break;
   }
   ctx->xf_first = false;
@@ -1529,7 +1540,7 @@ lsh_status basic_loop(lsh_ctx* ctx, int nload, double* x, LoadState* st, size_t 
   };
   for (int it = 0; it < maxit; ++it) {
     STCHK(run_iteration(ctx, 2, (long long)nload * 8 + ximode, iteration));
-    STCHK(progress_wait(ctx, hst, it, &any));
+    STCHK(progress_wait(ctx, hst, st_off, it, &any));
     if (!any) break;
   }
   return LSH_OK;
@@ -1600,7 +1611,7 @@ lsh_status mr_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
     }
     std::swap(v, vp);    // v_{k+1} now in the old v_{k-1} slot
     std::swap(w1, w2);   // w_k now in the old w_{k-2} slot
-    STCHK(progress_wait(ctx, hst, it, &any));
+    STCHK(progress_wait(ctx, hst, ctx->off.st_out, it, &any));
     if (!any) break;
   }
   return LSH_OK;
@@ -1665,7 +1676,7 @@ lsh_status sy_loop(lsh_ctx* ctx, int nload, double tol, int maxit, std::vector<L
       STCHK(check_launch(ctx, 0, "symmlq update"));
     }
     std::swap(v, vp);    // v_{k+1} now in the old v_{k-1} slot
-    STCHK(progress_wait(ctx, hst, it, &any));
+    STCHK(progress_wait(ctx, hst, ctx->off.st_out, it, &any));
     if (!any) break;
   }
   return LSH_OK;
