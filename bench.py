@@ -267,12 +267,9 @@ def run_ensemble():
         log(f"threads {threads}: {dt:.3f} s, {apps / dt:.3e} voxel-it/s")
     dt, apps, worst = res[4]
     # algorithmic bytes (scalar FP32 fields, c = 3): a CG voxel-iteration 15 c 4 + 4 = 184 B (one FP32
-    # coefficient per voxel), an FP64 refinement application 11 c 8 = 264 B; plane passes, which take
-    # every FP32 plane here and the FP64 ones to 128^2, save the two y passes, 4 c s of them
-    planes = os.environ.get("LSH_PLANE", "1")[:1] != "0"
-    b32 = 136 if planes else 184
-    alg = sum((b32 * r["applications_fp32"] + (168 if planes and m.n <= 128 else 264) * r["applications_fp64"])
-              * m.n ** 3 for r, m in zip(res_reps[4], members))
+    # coefficient per voxel), an FP64 refinement application 11 c 8 = 264 B
+    alg = sum((184 * r["applications_fp32"] + 264 * r["applications_fp64"]) * m.n ** 3
+              for r, m in zip(res_reps[4], members))
     gbs = alg / dt / 1e9
     del ctxs
     return {
@@ -281,9 +278,8 @@ def run_ensemble():
         "seconds": dt, "sequential_seconds": res[1][0], "concurrency_speedup": res[1][0] / dt,
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None,
-                     "basis": f"algorithmic bytes of the whole ensemble solve per second: {b32} B per FP32 CG "
-                              "voxel-iteration, 264 B per FP64 refinement voxel-application"
-                              + (" (168 B to 128^3)" if planes else "")},
+                     "basis": "algorithmic bytes of the whole ensemble solve per second: 184 B per FP32 CG "
+                              "voxel-iteration, 264 B per FP64 refinement voxel-application"},
         "worst_rel_residual": worst, "dtype": "f32+f64", "data": "synthetic",
         "config": {"workload": "48 cubes, sizes uniform over 64/96/128/160 (seed 0), a = exp(g), g a periodic "
                                "Gaussian field of correlation length 4, a0 = min(a)/2, filtered, 3 unit loads",
